@@ -264,11 +264,9 @@ nfvm_status nfvm_lambda2(nfvm_grid_t grid, double* lambda2);
  * J the Jacobian of E at the input state `state` (upwind selections and
  * clamps as the forward step takes them there).  All arrays device FP64
  * [nz][ny][nx], T absolute; outputs may not alias inputs.  Arithmetic in
- * FP64 whatever the grid's precision; the grid's fields are not touched.
- * The first call of this or nfvm_destroy_adjoint_device allocates 22 FP64
- * values per padded cell of scratch, kept until the grid is freed.  Runs on
- * the grid's stream and waits for it.  Errors: NFVM_E_INVAL for a null
- * pointer, NFVM_E_NOMEM. */
+ * FP64 whatever the grid's precision; the grid's fields are not touched and
+ * nothing is allocated.  Runs on the grid's stream and waits for it.
+ * Errors: NFVM_E_INVAL for a null pointer. */
 nfvm_status nfvm_explicit_adjoint_device(nfvm_grid_t grid, const nfvm_fields* state,
                                          const nfvm_fields* bar, nfvm_fields* out);
 
@@ -281,10 +279,9 @@ nfvm_status nfvm_explicit_adjoint_device(nfvm_grid_t grid, const nfvm_fields* st
  * adjoints kbar, wbar of k' and omega' this writes the adjoints of the five
  * inputs (state->u, v, w, k, omega; T and p not read, out->T and out->p not
  * written) at the input state.  All arrays device FP64 [nz][ny][nx]; outputs
- * may not alias inputs; FP64 arithmetic; scratch as for
- * nfvm_explicit_adjoint_device (shared).  Runs on the grid's stream and
- * waits for it.  Errors: NFVM_E_INVAL for a null pointer or tau < 0,
- * NFVM_E_NOMEM. */
+ * may not alias inputs; FP64 arithmetic; nothing is allocated.  Runs on the
+ * grid's stream and waits for it.  Errors: NFVM_E_INVAL for a null pointer or
+ * tau < 0. */
 nfvm_status nfvm_destroy_adjoint_device(nfvm_grid_t grid, const nfvm_fields* state, double tau,
                                         const double* kbar, const double* wbar,
                                         nfvm_fields* out);
@@ -306,8 +303,8 @@ nfvm_status nfvm_destroy_adjoint_device(nfvm_grid_t grid, const nfvm_fields* sta
  * stage's output, then at U.  All arrays device FP64 [nz][ny][nx], T
  * absolute; outputs may not alias inputs.  stats: NULL or two entries, the
  * forward and the adjoint solve.  The first call allocates 35 dense FP64
- * arrays of scratch (20 more with the Heun stage, plus the stage reverse
- * modes' scratch), kept until the grid is freed.  Runs on the grid's stream
+ * arrays of scratch (20 more with the Heun stage), kept until the grid is
+ * freed.  Runs on the grid's stream
  * and waits for it.  Errors: NFVM_E_INVAL for a null pointer; solve
  * statuses as nfvm_mg_solve_device (a diverged forward solve leaves `out`
  * unwritten). */

@@ -297,7 +297,6 @@ class GridT : public GridBase {
   // alternate between iterations
   void* dir[2] = {nullptr, nullptr};
   double* stage = nullptr;
-  double* adj_scratch = nullptr;  // reverse modes of the explicit and destruction steps
   double* adj_dense = nullptr;    // reverse mode of the whole step
   double* adj_heun = nullptr;     // ... and of its Heun explicit stage
   RedBuf red{};
@@ -787,18 +786,8 @@ class GridT : public GridBase {
       if (!q) throw Error{NFVM_E_INVAL, "the six output adjoints are required"};
     for (double* q : xb)
       if (!q) throw Error{NFVM_E_INVAL, "all seven input adjoint arrays are required"};
-    const size_t T = (size_t)g.total;
-    // (allocated on first use: 22 padded FP64 arrays)
-    if (!adj_scratch) adj_scratch = alloc<double>(22 * T, "adjoint scratch");
-    double* S = adj_scratch;
-    // (the Jacobian does not depend on p, which is therefore not packed)
-    const double* sd[7];
-    for (int f = 0; f < 7; ++f) {
-      sd[f] = f == 3 ? nullptr : S + f * T;
-      if (f != 3) launch_pack<double>(g, sp[f], S + f * T, f == 4 ? ph.T_ref : 0.0, stream);
-    }
-    launch_explicit_adjoint(g, ph, type, patches, sd, yb, S + 7 * T, S + 13 * T, S + 15 * T,
-                            S + 21 * T, xb, stream);
+    const double* s6[6] = {st.u, st.v, st.w, st.T, st.k, st.omega};
+    launch_explicit_adjoint(g, ph, type, patches, s6, yb, xb, stream);
     NFVM_CK(hipGetLastError());
     NFVM_CK(hipStreamSynchronize(stream));
   }
@@ -813,16 +802,7 @@ class GridT : public GridBase {
       if (!q) throw Error{NFVM_E_INVAL, "the adjoints of u, v, w, k and omega are required"};
     if (!kb || !wb) throw Error{NFVM_E_INVAL, "the adjoints of k and omega are required"};
     if (!(tau >= 0.0)) throw Error{NFVM_E_INVAL, "tau must be >= 0"};
-    const size_t T = (size_t)g.total;
-    if (!adj_scratch) adj_scratch = alloc<double>(22 * T, "adjoint scratch");
-    double* S = adj_scratch;
-    const double* sd[5];
-    for (int f = 0; f < 5; ++f) {
-      launch_pack<double>(g, sp[f], S + f * T, 0.0, stream);
-      sd[f] = S + f * T;
-    }
-    launch_destroy_adjoint(g, ph, type, patches, sd, tau, kb, wb, S + 5 * T, S + 11 * T, xb,
-                           stream);
+    launch_destroy_adjoint(g, ph, type, patches, sp, tau, kb, wb, xb, stream);
     NFVM_CK(hipGetLastError());
     NFVM_CK(hipStreamSynchronize(stream));
   }

@@ -10,19 +10,33 @@
 // The stage updates every fluid cell by dt times a sum of face fluxes, each a
 // function of the two cells of the face (a boundary face's outer values being
 // affine ghost rules of the inner cell, Sec. 2.7), plus cell sources that
-// read the central velocity gradient.  The transposed Jacobian is formed as
-// a gather, one thread per input cell, in two passes over padded FP64 arrays:
-//   1. per output cell: the weights dt * ybar of the outputs that the fluxes
-//      feed (zero where an output is not updated or is clamped at eps), the
-//      factor by which each output passes its own input (1, or 0 where k or
-//      omega is clamped), and 4 Lambda S_ab with Lambda = W_k nu_t + W_omega
-//      alpha, the weight of the strain-rate sources;
-//   2. per input cell: its own pass terms, then each face's flux derivatives
-//      with respect to this cell's values times the difference of the two
-//      cells' weights, the production terms of its own and of its
-//      neighbours' strain rates, buoyancy, and the closure chain rule.
-// Arithmetic in FP64 throughout.
+// read the central velocity gradient.  The transposed Jacobian at a cell is
+//   - the weights of each output cell: dt * ybar of the outputs that the
+//     fluxes feed (zero where an output is not updated or is clamped at eps),
+//     the factor by which each output passes its own input (1, or 0 where k
+//     or omega is clamped), and 4 Lambda S_ab with Lambda = W_k nu_t +
+//     W_omega alpha, the weight of the strain-rate sources;
+//   - gathered per input cell: its own pass terms, then each face's flux
+//     derivatives with respect to this cell's values times the difference of
+//     the two cells' weights, the production terms of its own and of its
+//     neighbours' strain rates, buoyancy, and the closure chain rule.
+// The destruction step's is of the same form (below).  Arithmetic in FP64
+// throughout.
+//
+// Each reverse mode is one kernel that reads every input once and writes every
+// output once: the weights live in registers and LDS only.  A workgroup of
+// 64 x RY threads walks the planes of a column tile, one column per
+// thread.  Lanes 1 .. 62 and every row form weights, lanes 2 .. 61 and rows
+// 1 .. RY - 2 have results: a tile is 60 x (RY - 2) columns and the
+// rest recompute the weights its results read (1.4 times the weight
+// arithmetic, no memory traffic beyond the caches).  The x neighbours come
+// from the adjacent lanes of the wave (DPP shifts), the y neighbours from LDS
+// rows, the z neighbours from the walk: the weights are formed one plane
+// ahead, and a cell's result is stored once the plane above has been
+// weighed.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "nfvm_device.hpp"
 
@@ -30,6 +44,11 @@ namespace nfvm {
 
 namespace {
 constexpr int ABX = 64, ABY = 4;
+// Rows of a workgroup: as many waves as its registers leave room for on one
+// CU (explicit stage 235 VGPRs: 8 waves; destruction 158: 12, with 10 rows of
+// results in 12 instead of 6 in 8: 965 -> 780 us on the 512 x 256 x 128 room).
+constexpr int EX_RY = 8, DS_RY = 12;
+constexpr int ADJ_TX = 60;           // columns of a tile along x
 
 // transported fields in flux order and their ghost-rule codes
 constexpr int NF = 6;  // u v w theta k omega
@@ -37,444 +56,679 @@ __device__ __forceinline__ int ghost_code(int f) {
   return f < 3 ? G_U + f : (f == 3 ? G_T : (f == 4 ? G_K : G_OM));
 }
 
-// The cell of this thread.  The launch is one-dimensional, 8 * per
-// workgroups of ABX x ABY threads over the list of (column tile, plane)
-// entries, planes fastest; workgroup b runs on XCD b % 8 and takes entry
-// (b % 8) * per + b / 8, so the workgroups in flight on one XCD hold
-// consecutive planes of the same column tiles and the planes above and below
-// that each cell reads are in that XCD's L2.
-__device__ __forceinline__ bool adj_cell(const Geom& g, int& i, int& j, int& k) {
-  const int ntx = (g.nx + ABX - 1) / ABX, nty = (g.ny + ABY - 1) / ABY;
-  const long long total = (long long)ntx * nty * g.nz;
-  const long long per = gridDim.x >> 3;
-  const long long t = (long long)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
-  if (t >= total) return false;
-  k = (int)(t % g.nz);
-  const long long c = t / g.nz;
-  i = (int)(c % ntx) * ABX + threadIdx.x;
-  j = (int)(c / ntx) * ABY + threadIdx.y;
-  return i < g.nx && j < g.ny;
-}
-
-// workgroups of the launches that use adj_cell (a multiple of 8)
-inline dim3 adj_grid(const Geom& g) {
-  const long long total =
-      (long long)((g.nx + ABX - 1) / ABX) * ((g.ny + ABY - 1) / ABY) * g.nz;
-  return dim3((unsigned)(8 * ((total + 7) / 8)));
-}
-
-struct AdjCell {
-  double v[NF], nu;
-  uint8_t t;
+// What the kernels read of the grid and its physics; the reciprocals are
+// formed once on the host (a division costs a thread a dozen instructions).
+struct AdjParams {
+  int nx, ny, nz, d3, sx, sxy, off;
+  int ntx, nty, cz, total;  // column tiles, planes per chunk, tiles in all
+  double ih[3], ih2[3];     // 1 / h, 1 / (2 h)
+  double nu, inu, alpha_T, is3, is4, is5, dt, T_ref, bg[3];
+  int komega, energy, buoyancy;
 };
 
-// nu_t = alpha*(Re_t) k / omega-hat and its partial derivatives in k and
-// omega (eqs. a_star and Re_t with alpha*_inf = 1, alpha*_0 = beta_i / 3)
-__device__ __forceinline__ void closure_grad(double nu, double k, double w, double& nt,
-                                             double& dk, double& dw) {
-  const bool live = w > C_EPS;
-  const double oh = live ? w : C_EPS;
-  const double ret = k / (nu * oh);
-  const double x = ret * (1.0 / C_R_K);
-  const double a0 = C_BETA_I / 3.0;
-  const double as = (a0 + x) / (1.0 + x);
-  const double das = (1.0 - a0) * (1.0 / C_R_K) / ((1.0 + x) * (1.0 + x));  // d as / d ret
-  nt = as * k / oh;
-  dk = das * (1.0 / (nu * oh)) * k / oh + as / oh;
-  dw = live ? das * (-ret / oh) * k / oh - as * k / (oh * oh) : 0.0;
+// Chunks of planes per column tile.  A chunk of cz planes takes cz + 2 steps
+// of its workgroup (the planes of weights on both sides) and about one more
+// to start and end, and the 256 CUs hold one workgroup each at a time (its
+// registers): the count that makes the rounds times the steps shortest.
+constexpr int ADJ_CUS = 256;
+int adj_chunks(int cols, int nz) {
+  long long best = -1;
+  int chunks = 1;
+  // (more chunks than this leave every CU busy whatever the tail)
+  const int most = std::min(nz, 64 * ADJ_CUS / std::min(cols, 64 * ADJ_CUS) + 1);
+  for (int c = 1; c <= most; ++c) {
+    const int cz = (nz + c - 1) / c;
+    if ((nz + cz - 1) / cz != c) continue;  // (the same cz as a smaller count)
+    const long long t = ((long long)cols * c + ADJ_CUS - 1) / ADJ_CUS * (cz + 3);
+    if (best < 0 || t < best) {
+      best = t;
+      chunks = c;
+    }
+  }
+  return chunks;
 }
 
-// alpha of the omega production (eq. a with eqs. k_gen, o_gen) and its
-// derivatives in k and omega
-__device__ __forceinline__ void alpha_grad(double nu, double k, double w, double& al,
-                                           double& dk, double& dw) {
-  const bool live = w > C_EPS;
-  const double oh = live ? w : C_EPS;
-  const double ret = k / (nu * oh);
-  const double xr = ret * (1.0 / C_R_W);
-  al = C_A_INF * (C_A0 + xr) / (1.0 + xr);
-  const double da = C_A_INF * (1.0 - C_A0) * (1.0 / C_R_W) / ((1.0 + xr) * (1.0 + xr));
-  dk = da / (nu * oh);
-  dw = live ? da * (-ret / oh) : 0.0;
+AdjParams adj_params(const Geom& g, const Phys& ph, int rows) {
+  AdjParams p;
+  p.nx = g.nx;
+  p.ny = g.ny;
+  p.nz = g.nz;
+  p.d3 = g.dim == 3;
+  p.sx = g.sx;
+  p.sxy = g.sxy;
+  p.off = g.off;
+  p.ntx = (g.nx + ADJ_TX - 1) / ADJ_TX;
+  p.nty = (g.ny + rows - 3) / (rows - 2);
+  const int cols = p.ntx * p.nty;
+  const int chunks = adj_chunks(cols, g.nz);
+  p.cz = (g.nz + chunks - 1) / chunks;
+  p.total = cols * ((g.nz + p.cz - 1) / p.cz);
+  const double h[3] = {g.hx, g.hy, g.hz};
+  for (int d = 0; d < 3; ++d) {
+    p.ih[d] = 1.0 / h[d];
+    p.ih2[d] = 0.5 / h[d];
+    p.bg[d] = -ph.beta_T * ph.g[d];
+  }
+  p.nu = ph.nu;
+  p.inu = 1.0 / ph.nu;
+  p.alpha_T = ph.alpha_T;
+  p.is3 = ph.inv_Pr_t;
+  p.is4 = ph.inv_sigma_k;
+  p.is5 = ph.inv_sigma_w;
+  p.dt = ph.dt;
+  p.T_ref = ph.T_ref;
+  p.komega = ph.komega;
+  p.energy = ph.energy;
+  p.buoyancy = ph.buoyancy;
+  return p;
+}
+inline dim3 adj_grid(const AdjParams& p) { return dim3((unsigned)((p.total + 7) / 8 * 8)); }
+
+// The tile of this workgroup; workgroup b runs on XCD b % 8, and each XCD
+// takes a contiguous range of tiles (x fastest), whose halos overlap in its L2.
+__device__ __forceinline__ bool adj_tile(const AdjParams& p, int& tx, int& ty, int& tz) {
+  const int per = gridDim.x >> 3;
+  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if (t >= p.total) return false;
+  tx = t % p.ntx;
+  const int r = t / p.ntx;
+  ty = r % p.nty;
+  tz = r / p.nty;
+  return true;
 }
 
-// (the stage's Jacobian does not depend on p: it enters the momentum
-// update linearly, so the state's p is not read)
-struct AdjState {
-  const double *u, *v, *w, *T, *k, *om;  // padded; T as T - T_ref
-  const double* nu;  // nu_t of the fluid cells (k-omega only), padded
-};
-
-__device__ __forceinline__ AdjCell load_adj(const AdjState& S, const uint8_t* type, int N,
-                                            const Phys& ph) {
-  AdjCell c;
-  c.t = type[N];
-  c.v[0] = S.u[N];
-  c.v[1] = S.v[N];
-  c.v[2] = S.w[N];
-  c.v[3] = S.T[N];
-  c.v[4] = S.k[N];
-  c.v[5] = S.om[N];
-  c.nu = ph.komega && is_fluid(c.t) ? S.nu[N] : 0.0;
-  return c;
+// Element at byte offset vi of a row given by a scalar pointer (kept opaque,
+// so that the access takes a scalar base and a 32-bit lane offset rather than
+// a 64-bit address per lane and array).
+#define ADJ_GLOBAL __attribute__((address_space(1)))
+template <class T>
+__device__ __forceinline__ ADJ_GLOBAL T* row_at(T* row, unsigned vi) {
+  ADJ_GLOBAL char* q = (ADJ_GLOBAL char*)(ADJ_GLOBAL T*)row;
+  asm("" : "+s"(q), "+v"(vi));
+  return (ADJ_GLOBAL T*)(q + vi);
 }
 
-// values across a boundary face, from the fluid cell P
-__device__ __forceinline__ AdjCell ghost_adj(const DevPatch& pp, const AdjCell& P, int komega,
-                                             uint8_t t) {
-  AdjCell g;
-  for (int f = 0; f < NF; ++f) g.v[f] = ghost<double>(pp, ghost_code(f), P.v[f], komega);
-  g.nu = ghost<double>(pp, G_NUT, P.nu, komega);
-  g.t = t;
-  return g;
+// Type byte of cell (i, r, m) (vt: i + 1, clamped to the padded row; pi: i
+// was in it), solid past the padded array.
+__device__ __forceinline__ int adj_type(const AdjParams& p, const uint8_t* type, unsigned vt,
+                                        bool pi, int r, int m) {
+  const int gz = p.d3 ? 1 : 0;
+  const int rq = min(max(r, -1), p.ny), mq = min(max(m, -gz), p.nz - 1 + gz);
+  const int t = *row_at(type + (p.off + mq * p.sxy + rq * p.sx - 1), vt);
+  return pi && r == rq && m == mq ? t : PID_SOLID;
 }
 
+// The value of the next lower (higher) lane of the wave; every lane of the
+// wave must take part, and lane 0 (63) gets 0.
+template <int CTRL>
+__device__ __forceinline__ int lane_shift(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v) {
+  return __hiloint2double(lane_shift<CTRL>(__double2hiint(v)),
+                          lane_shift<CTRL>(__double2loint(v)));
+}
+constexpr int WAVE_SHR1 = 0x138, WAVE_SHL1 = 0x130;
+template <class T>
+__device__ __forceinline__ T lane_below(T v) {
+  return lane_shift<WAVE_SHR1>(v);
+}
+template <class T>
+__device__ __forceinline__ T lane_above(T v) {
+  return lane_shift<WAVE_SHL1>(v);
+}
+
+// d(ghost value) / d(own value) across a boundary face
 __device__ __forceinline__ double slope(const DevPatch& pp, int code, int komega) {
   return ghost<double>(pp, code, 1.0, komega) - ghost<double>(pp, code, 0.0, komega);
 }
 
-__device__ __forceinline__ void field_coef(const Phys& ph, double (&g0)[NF], double (&is)[NF]) {
-  g0[0] = g0[1] = g0[2] = ph.nu;
-  g0[3] = ph.alpha_T;
-  g0[4] = g0[5] = ph.nu;
+struct ExplicitIo {
+  const double *u, *v, *w, *T, *k, *om;        // state, dense (T absolute)
+  const double *ybu, *ybv, *ybw, *ybT, *ybk, *ybo;  // adjoints of the outputs, dense
+  double *xu, *xv, *xw, *xp, *xT, *xk, *xo;    // adjoints of the inputs, dense
+};
+
+struct ExplicitArgs {
+  ExplicitIo io;  // (first: read again from the kernel arguments where used)
+  AdjParams p;
+  const uint8_t* type;
+  const DevPatch* pt;
+};
+
+// The array pointers, loaded from the kernel-argument segment (through the
+// scalar cache) at each use: with the parameters they are more than the
+// scalar registers hold, and kept ones are spilled to vector lanes.
+__device__ __forceinline__ const __attribute__((address_space(4))) ExplicitIo* explicit_io() {
+  auto q = (const __attribute__((address_space(4))) ExplicitIo*)
+      __builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(q));
+  return q;
+}
+
+// One cell of the walk: u v w theta k omega, nu_t and the type byte.
+struct AdjCell {
+  double v[NF], nu;
+  int t;
+};
+
+// The closures of one fluid cell: nu_t with its derivatives in k and omega
+// (eqs. a_star, Re_t), and alpha of the omega production (eq. a) with its own.
+struct AdjClosure {
+  double nt, dk, dw, al, ak, aw;
+};
+
+// Partial result of one cell.
+struct AdjAcc {
+  double x[NF], nb, pb;  // adjoints of the six fields, of nu_t and of p
+};
+
+__device__ __forceinline__ void field_coef(const AdjParams& p, double (&g0)[NF],
+                                           double (&is)[NF]) {
+  g0[0] = g0[1] = g0[2] = g0[4] = g0[5] = p.nu;
+  g0[3] = p.alpha_T;
   is[0] = is[1] = is[2] = 1.0;
-  is[3] = ph.inv_Pr_t;
-  is[4] = ph.inv_sigma_k;
-  is[5] = ph.inv_sigma_w;
+  is[3] = p.is3;
+  is[4] = p.is4;
+  is[5] = p.is5;
 }
 
-// central velocity gradient G[a][b] = d u_a / d x_b at fluid cell P with
-// boundary ghosts; N[b][s] are the neighbours (s = 0: -, 1: +)
-__device__ __forceinline__ void adj_gradient(const Geom& g, const AdjCell& P,
-                                             const AdjCell (&N)[3][2], double (&G)[3][3]) {
-  const double ih2[3] = {0.5 / g.hx, 0.5 / g.hy, 0.5 / g.hz};
-  #pragma unroll
-  for (int a = 0; a < 3; ++a)
-    #pragma unroll
-    for (int b = 0; b < 3; ++b)
-      G[a][b] = (a < g.dim && b < g.dim) ? (N[b][1].v[a] - N[b][0].v[a]) * ih2[b] : 0.0;
-}
-
-// the six neighbours of fluid cell P, ghosts substituted
-__device__ __forceinline__ void adj_neighbours(const Geom& g, const Phys& ph, const AdjState& S,
-                                               const uint8_t* type, const DevPatch* pt, int P,
-                                               const AdjCell& c, AdjCell (&N)[3][2]) {
-  const int st[3] = {1, g.sx, g.sxy};
-  #pragma unroll
-  for (int d = 0; d < 3; ++d)
-    #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      if (d >= g.dim) {
-        N[d][s] = c;
-        continue;
+// The face between the fluid cells lo and up along D: the flux derivatives
+// with respect to both cells' values times g = (W_lo - W_up) / h, the weight
+// of the flux in the outputs, added to L and U.
+template <int D>
+__device__ __forceinline__ void face_adj(const AdjParams& p, const double (&lo)[NF], double nlo,
+                                         const double (&Wl)[NF], const double (&up)[NF],
+                                         double nup, const double (&Wu)[NF], AdjAcc& L,
+                                         AdjAcc& U) {
+  double g0[NF], is[NF];
+  field_coef(p, g0, is);
+  const double ihd = p.ih[D];
+  const double Uf = 0.5 * (lo[D] + up[D]);
+  const double nutf = 0.5 * (nlo + nup);
+  // the upwind value is the lower cell's for Uf >= 0
+  const bool pos = Uf >= 0.0;
+  const double Up = pos ? Uf : 0.0, Un = pos ? 0.0 : Uf;
+  double dU = 0.0, dn = 0.0;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const double g = ihd * (Wl[f] - Wu[f]);
+    const double df = (g0[f] + nutf * is[f]) * ihd;
+    L.x[f] -= g * (Up + df);
+    U.x[f] += g * (df - Un);
+    dU -= g * ((pos ? lo[f] : up[f]) + (f == 3 ? p.T_ref : 0.0));
+    dn += g * is[f] * (up[f] - lo[f]);
+    if (f == D) {
+      // -(p + 2/3 k)_f on the faces normal to momentum component D
+      L.pb -= 0.5 * g;
+      U.pb -= 0.5 * g;
+      if (p.komega) {
+        L.x[4] -= g * (1.0 / 3.0);
+        U.x[4] -= g * (1.0 / 3.0);
       }
-      const int Q = P + (s ? 1 : -1) * st[d];
-      const uint8_t tq = type[Q];
-      N[d][s] = is_fluid(tq) ? load_adj(S, type, Q, ph) : ghost_adj(pt[tq & 0x7f], c, ph.komega, tq);
     }
-}
-
-// neighbour s (0: -, 1: +) of fluid cell P along d < dim, ghost substituted
-// (one element of adj_neighbours, loaded where it is used)
-__device__ __forceinline__ AdjCell adj_neighbour(const Geom& g, const Phys& ph, const AdjState& S,
-                                                 const uint8_t* type, const DevPatch* pt, int P,
-                                                 const AdjCell& c, int d, int s) {
-  const int Q = P + (s ? 1 : -1) * (d == 0 ? 1 : (d == 1 ? g.sx : g.sxy));
-  const uint8_t tq = type[Q];
-  return is_fluid(tq) ? load_adj(S, type, Q, ph) : ghost_adj(pt[tq & 0x7f], c, ph.komega, tq);
-}
-
-// the central velocity gradient of adj_gradient, from the neighbours'
-// velocities alone
-__device__ __forceinline__ void adj_gradient_at(const Geom& g, const Phys& ph, const AdjState& S,
-                                                const uint8_t* type, const DevPatch* pt, int P,
-                                                const AdjCell& c, double (&G)[3][3]) {
-  const double ih2[3] = {0.5 / g.hx, 0.5 / g.hy, 0.5 / g.hz};
-  const double* vel[3] = {S.u, S.v, S.w};
-  #pragma unroll
-  for (int a = 0; a < 3; ++a)
-    #pragma unroll
-    for (int b = 0; b < 3; ++b) G[a][b] = 0.0;
-  #pragma unroll
-  for (int b = 0; b < 3; ++b) {
-    if (b >= g.dim) continue;
-    double vn[2][3];
-    #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int Q = P + (s ? 1 : -1) * (b == 0 ? 1 : (b == 1 ? g.sx : g.sxy));
-      const uint8_t tq = type[Q];
-      #pragma unroll
-      for (int a = 0; a < 3; ++a)
-        vn[s][a] = is_fluid(tq) ? vel[a][Q]
-                                : ghost<double>(pt[tq & 0x7f], G_U + a, c.v[a], ph.komega);
-    }
-    #pragma unroll
-    for (int a = 0; a < 3; ++a)
-      if (a < g.dim) G[a][b] = (vn[1][a] - vn[0][a]) * ih2[b];
   }
+  dU *= 0.5;
+  dn *= 0.5 * ihd;
+  L.x[D] += dU;
+  U.x[D] += dU;
+  L.nb += dn;
+  U.nb += dn;
+}
+
+// The boundary face of fluid cell c on side s (0: -, 1: +) along d, whose
+// outer values are ghosts of c: the flux derivatives through both sides, and
+// this cell's own strain rate through the ghost velocities (lam: 4 Lambda
+// S_ad of the cell, a = 0 .. 2).
+__device__ __forceinline__ void ghost_face_adj(const AdjParams& p, const DevPatch& pp, int d,
+                                               int s, const AdjCell& c, const double (&Wc)[NF],
+                                               const double (&lam)[3], AdjAcc& A) {
+  double g0[NF], is[NF];
+  field_coef(p, g0, is);
+  const int komega = p.komega;
+  const double sg = s ? 1.0 : -1.0;
+  const double ihd = d == 0 ? p.ih[0] : (d == 1 ? p.ih[1] : p.ih[2]);
+  double n[NF], gs[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    n[f] = ghost<double>(pp, ghost_code(f), c.v[f], komega);
+    gs[f] = slope(pp, ghost_code(f), komega);
+  }
+  const double nn = ghost<double>(pp, G_NUT, c.nu, komega);
+  const double gp = slope(pp, G_P, komega), gn = slope(pp, G_NUT, komega);
+  auto at = [&](const double (&a)[NF]) { return d == 0 ? a[0] : (d == 1 ? a[1] : a[2]); };
+  const double Uf = 0.5 * (at(c.v) + at(n));
+  const double nutf = 0.5 * (c.nu + nn);
+  const bool own_up = (Uf >= 0.0) == (s == 1);
+  double dU = 0.0, dn = 0.0;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const double wf = sg * ihd * Wc[f];
+    const double lower = s ? c.v[f] : n[f], upper = s ? n[f] : c.v[f];
+    const double up = Uf >= 0.0 ? lower : upper;
+    const double gam = g0[f] + nutf * is[f];
+    const double dup = own_up ? 1.0 : gs[f];
+    A.x[f] += wf * (-Uf * dup + gam * sg * (gs[f] - 1.0) * ihd);
+    dU += wf * (-up - (f == 3 ? p.T_ref : 0.0));
+    dn += wf * is[f] * (upper - lower) * ihd;
+  }
+  const double dUo = dU * 0.5 * (1.0 + at(gs));
+  const double wd = sg * ihd * at(Wc);
+  const double f2 = sg * (d == 0 ? p.ih2[0] : (d == 1 ? p.ih2[1] : p.ih2[2]));
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (a == d) A.x[a] += dUo;
+    if (komega && (a < 2 || p.d3)) A.x[a] += lam[a] * f2 * gs[a];
+  }
+  A.nb += dn * 0.5 * (1.0 + gn);
+  A.pb += wd * -0.5 * (1.0 + gp);
+  if (komega) A.x[4] += wd * (-1.0 / 3.0) * (1.0 + gs[4]);
+}
+
+// alpha* = (a0 + x) / (1 + x), x = Re_t / R_k; alpha = a_inf (A0 + y) / (1 + y),
+// y = Re_t / R_w; Re_t = k / (nu omega-hat).
+__device__ __forceinline__ void adj_closure(const AdjParams& p, double k, double w,
+                                            AdjClosure& c) {
+  const bool live = w > C_EPS;
+  const double ioh = 1.0 / (live ? w : C_EPS);
+  const double ki = k * ioh, ret = ki * p.inu, ri = ret * ioh;
+  const double a0 = C_BETA_I / 3.0;
+  const double x = ret * (1.0 / C_R_K), y = ret * (1.0 / C_R_W);
+  const double ix = 1.0 / (1.0 + x), iy = 1.0 / (1.0 + y);
+  const double as = (a0 + x) * ix;
+  const double das = (1.0 - a0) * (1.0 / C_R_K) * ix * ix;  // d as / d Re_t
+  const double da = C_A_INF * (1.0 - C_A0) * (1.0 / C_R_W) * iy * iy;
+  c.nt = as * ki;
+  c.dk = das * (p.inu * ioh) * ki + as * ioh;
+  c.dw = live ? -(das * ri) * ki - as * ki * ioh : 0.0;
+  c.al = C_A_INF * (C_A0 + y) * iy;
+  c.ak = da * p.inu * ioh;
+  c.aw = live ? -(da * ri) : 0.0;
+}
+
+__device__ __forceinline__ double adj_nut(const AdjParams& p, const AdjCell& c) {
+  AdjClosure q;
+  q.nt = 0.0;
+  if (p.komega && is_fluid((uint8_t)c.t)) adj_closure(p, c.v[4], c.v[5], q);
+  return q.nt;
 }
 }  // namespace
 
-// nu_t of every fluid cell (the closure of its k and omega), read by both
-// passes at a cell and its six neighbours instead of being formed there.
-__global__ __launch_bounds__(ABX* ABY) void k_adj_nut(Geom g, Phys ph,
-                                                     const uint8_t* __restrict__ type,
-                                                     const double* __restrict__ kk,
-                                                     const double* __restrict__ om,
-                                                     double* __restrict__ nu) {
-  int i, j, k;
-  if (!adj_cell(g, i, j, k)) return;
-  const int P = g.idx(i, j, k);
-  double nt = 0.0, dk, dw;
-  if (is_fluid(type[P])) closure_grad(ph.nu, kk[P], om[P], nt, dk, dw);
-  nu[P] = nt;
-}
-
-// Pass 1: weights of each output cell.  W: six padded arrays (u v w theta k
-// omega), pass: two (k, omega), L4S: six (S00 S11 S22 S01 S02 S12 times
-// 4 Lambda).  ybar: dense [nz][ny][nx] adjoints of the six outputs.
-__global__ __launch_bounds__(ABX* ABY) void k_adj_ex_weights(
-    Geom g, Phys ph, const uint8_t* __restrict__ type, const DevPatch* __restrict__ pt,
-    AdjState S, const double* __restrict__ ybu, const double* __restrict__ ybv,
-    const double* __restrict__ ybw, const double* __restrict__ ybT,
-    const double* __restrict__ ybk, const double* __restrict__ ybo, double* __restrict__ W,
-    double* __restrict__ pass, double* __restrict__ L4S) {
-  int i, j, k;
-  if (!adj_cell(g, i, j, k)) return;
-  const int P = g.idx(i, j, k);
-  const size_t D = ((size_t)k * g.ny + j) * g.nx + i;
-  const size_t T = (size_t)g.total;
-  const uint8_t tp = type[P];
-  // formed in registers and stored once (zero weights and pass 1 where the
-  // cell is not fluid)
-  double Wv[NF] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, Lv[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  double ps[2] = {1.0, 1.0};
-  [&]() {
-    if (!is_fluid(tp)) return;
-    const double dt = ph.dt;
-    const double yb[NF] = {ybu[D], ybv[D], ybw[D], ybT[D], ybk[D], ybo[D]};
-    #pragma unroll
-    for (int a = 0; a < 3; ++a) Wv[a] = a < g.dim ? dt * yb[a] : 0.0;
-    Wv[3] = ph.energy ? dt * yb[3] : 0.0;
-    if (!ph.komega) return;
-    const AdjCell c = load_adj(S, type, P, ph);
-    AdjCell N[3][2];
-    adj_neighbours(g, ph, S, type, pt, P, c, N);
-    double g0[NF], is[NF];
-    field_coef(ph, g0, is);
-    const double ih[3] = {1.0 / g.hx, 1.0 / g.hy, 1.0 / g.hz};
-    double rk = 0.0, rw = 0.0;
-    #pragma unroll
-    for (int d = 0; d < 3; ++d)
-      #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        if (d >= g.dim) continue;
-        const AdjCell& n = N[d][s];
-        const double sg = s ? 1.0 : -1.0;
-        const double Uf = 0.5 * (c.v[d] + n.v[d]);
-        const double nutf = 0.5 * (c.nu + n.nu);
-        #pragma unroll
-        for (int f = 4; f < 6; ++f) {
-          const double lower = s ? c.v[f] : n.v[f], upper = s ? n.v[f] : c.v[f];
-          const double up = Uf >= 0.0 ? lower : upper;
-          const double F = -Uf * up + (g0[f] + nutf * is[f]) * (upper - lower) * ih[d];
-          (f == 4 ? rk : rw) += sg * F * ih[d];
-        }
-      }
-    double G[3][3];
-    adj_gradient(g, c, N, G);
-    double Sab[6];
-    Sab[0] = G[0][0];
-    Sab[1] = G[1][1];
-    Sab[2] = G[2][2];
-    Sab[3] = 0.5 * (G[0][1] + G[1][0]);
-    Sab[4] = 0.5 * (G[0][2] + G[2][0]);
-    Sab[5] = 0.5 * (G[1][2] + G[2][1]);
-    const double S2 = 2.0 * (Sab[0] * Sab[0] + Sab[1] * Sab[1] + Sab[2] * Sab[2] +
-                             2.0 * (Sab[3] * Sab[3] + Sab[4] * Sab[4] + Sab[5] * Sab[5]));
-    double al, dak, daw;
-    alpha_grad(ph.nu, c.v[4], c.v[5], al, dak, daw);
-    const double kn = c.v[4] + dt * (rk + c.nu * S2);
-    const double wn = c.v[5] + dt * (rw + al * S2);
-    const bool pk = kn > C_EPS;
-    const bool fixed = (tp & FIXED_BIT) != 0;
-    const bool pw = fixed || wn > C_EPS;
-    const double Wk = pk ? dt * yb[4] : 0.0;
-    const double Ww = (!fixed && pw) ? dt * yb[5] : 0.0;
-    Wv[4] = Wk;
-    Wv[5] = Ww;
-    ps[0] = pk ? 1.0 : 0.0;
-    ps[1] = pw ? 1.0 : 0.0;
-    const double lam4 = 4.0 * (Wk * c.nu + Ww * al);
-    #pragma unroll
-    for (int q = 0; q < 6; ++q) Lv[q] = lam4 * Sab[q];
-  }();
-  #pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    W[f * T + P] = Wv[f];
-    L4S[f * T + P] = Lv[f];
-  }
-  pass[P] = ps[0];
-  pass[T + P] = ps[1];
-}
-
-// Pass 2: the adjoints of the inputs, dense [nz][ny][nx]: xb = {u v w p T k omega}.
-__global__ __launch_bounds__(ABX* ABY) void k_adj_ex_gather(
-    Geom g, Phys ph, const uint8_t* __restrict__ type, const DevPatch* __restrict__ pt,
-    AdjState S, const double* __restrict__ ybu, const double* __restrict__ ybv,
-    const double* __restrict__ ybw, const double* __restrict__ ybT,
-    const double* __restrict__ ybk, const double* __restrict__ ybo,
-    const double* __restrict__ W, const double* __restrict__ pass,
-    const double* __restrict__ L4S, double* __restrict__ xu, double* __restrict__ xv,
-    double* __restrict__ xw, double* __restrict__ xp, double* __restrict__ xT,
-    double* __restrict__ xk, double* __restrict__ xo) {
-  int i, j, k;
-  if (!adj_cell(g, i, j, k)) return;
-  const int P = g.idx(i, j, k);
-  const size_t D = ((size_t)k * g.ny + j) * g.nx + i;
-  const size_t T = (size_t)g.total;
-  const uint8_t tp = type[P];
-  // each output passes its own input (k and omega unless clamped)
-  double xb[NF] = {ybu[D], ybv[D], ybw[D], ybT[D], ybk[D] * pass[P], ybo[D] * pass[T + P]};
-  double pb = 0.0, nb = 0.0;  // adjoints of p and of nu_t at this cell
-  if (is_fluid(tp)) {
-    const AdjCell c = load_adj(S, type, P, ph);
-    double g0[NF], is[NF];
-    field_coef(ph, g0, is);
-    const int st[3] = {1, g.sx, g.sxy};
-    const double ih[3] = {1.0 / g.hx, 1.0 / g.hy, 1.0 / g.hz};
-    double Wc[NF];
-    #pragma unroll
-    for (int f = 0; f < NF; ++f) Wc[f] = W[f * T + P];
-    const int komega = ph.komega;
-    // faces
-    #pragma unroll
-    for (int d = 0; d < 3; ++d)
-      #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        if (d >= g.dim) continue;
-        const AdjCell n = adj_neighbour(g, ph, S, type, pt, P, c, d, s);
-        const double sg = s ? 1.0 : -1.0;
-        const bool nf = is_fluid(n.t);
-        const int Q = P + (s ? 1 : -1) * st[d];
-        // d(outer value) / d(own value) across this face
-        double gs[NF], gp = 0.0, gn = 0.0;
-        double wf[NF];
-        if (nf) {
-          #pragma unroll
-          for (int f = 0; f < NF; ++f) {
-            gs[f] = 0.0;
-            wf[f] = sg * ih[d] * (Wc[f] - W[f * T + Q]);
-          }
-        } else {
-          const DevPatch& pp = pt[n.t & 0x7f];
-          #pragma unroll
-          for (int f = 0; f < NF; ++f) {
-            gs[f] = slope(pp, ghost_code(f), komega);
-            wf[f] = sg * ih[d] * Wc[f];
-          }
-          gp = slope(pp, G_P, komega);
-          gn = slope(pp, G_NUT, komega);
-        }
-        const double Uf = 0.5 * (c.v[d] + n.v[d]);
-        const double nutf = 0.5 * (c.nu + n.nu);
-        // the upwind value is this cell's when the face velocity points away
-        // from it (lower cell for Uf >= 0)
-        const bool own_up = (Uf >= 0.0) == (s == 1);
-        double dUf = 0.0, dnut = 0.0;
-        #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          const double lower = s ? c.v[f] : n.v[f], upper = s ? n.v[f] : c.v[f];
-          const double up = Uf >= 0.0 ? lower : upper;
-          const double gam = g0[f] + nutf * is[f];
-          const double dup = own_up ? 1.0 : gs[f];
-          // d F / d phi_own, d F / d U_f, d F / d nut_f
-          xb[f] += wf[f] * (-Uf * dup + gam * sg * (gs[f] - 1.0) * ih[d]);
-          dUf += wf[f] * (-up - (f == 3 ? ph.T_ref : 0.0));
-          dnut += wf[f] * is[f] * (upper - lower) * ih[d];
-        }
-        xb[d] += dUf * 0.5 * (1.0 + gs[d]);
-        nb += dnut * 0.5 * (1.0 + gn);
-        // -(p + 2/3 k)_f on the faces normal to momentum component d
-        pb += wf[d] * -0.5 * (1.0 + (nf ? 0.0 : gp));
-        if (komega) xb[4] += wf[d] * (-1.0 / 3.0) * (1.0 + gs[4]);
-      }
-    // buoyancy -beta_T theta g_a
-    if (ph.buoyancy)
-      #pragma unroll
-      for (int a = 0; a < 3; ++a)
-        if (a < g.dim) xb[3] += Wc[a] * -ph.beta_T * ph.g[a];
-    if (komega) {
-      // production nu_t S^2 and alpha S^2 at this cell
-      double G[3][3];
-      adj_gradient_at(g, ph, S, type, pt, P, c, G);
-      double S2 = 0.0;
-      #pragma unroll
-      for (int a = 0; a < 3; ++a)
-        #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-          const double sab = 0.5 * (G[a][b] + G[b][a]);
-          S2 += sab * sab;
-        }
-      S2 *= 2.0;
-      double al, dak, daw;
-      alpha_grad(ph.nu, c.v[4], c.v[5], al, dak, daw);
-      nb += Wc[4] * S2;
-      xb[4] += Wc[5] * S2 * dak;
-      xb[5] += Wc[5] * S2 * daw;
-      // strain rates that read this cell's velocity: a neighbour's across the
-      // face (its own 4 Lambda S_ab), or this cell's own through a ghost
-      const double ih2[3] = {0.5 / g.hx, 0.5 / g.hy, 0.5 / g.hz};
-      const int sidx[3][3] = {{0, 3, 4}, {3, 1, 5}, {4, 5, 2}};
-      #pragma unroll
-      for (int b = 0; b < 3; ++b)
-        #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          if (b >= g.dim) continue;
-          const double sg = s ? 1.0 : -1.0;
-          const int Q = P + (s ? 1 : -1) * st[b];
-          const uint8_t tq = type[Q];
-          if (is_fluid(tq)) {
-            // this cell is the neighbour of Q on Q's side -sg along b
-            #pragma unroll
-            for (int a = 0; a < 3; ++a)
-              if (a < g.dim) xb[a] += L4S[sidx[a][b] * T + Q] * -sg * ih2[b];
-          } else {
-            const DevPatch& pp = pt[tq & 0x7f];
-            #pragma unroll
-            for (int a = 0; a < 3; ++a)
-              if (a < g.dim)
-                xb[a] += L4S[sidx[a][b] * T + P] * sg * ih2[b] * slope(pp, G_U + a, komega);
-          }
-        }
+// The explicit stage's reverse mode: 153 bytes per cell (thirteen dense arrays
+// in and seven out, with the type byte: it was 603 with the state packed and
+// the weights of every cell stored by one pass and gathered by another).
+// Bound by its FP64 instructions and the two waves per SIMD that its live
+// values leave (about 900 vector instructions per cell and plane): on the
+// 512 x 256 x 128 room 1.52 ms per call, 1.7 TB/s of those bytes, from 3.65 ms
+// for the two passes.  Measured and slower or no faster: predicated loads with
+// zeroed defaults (1.88 ms, spills), 6 rows (2.03), 64-bit lane addresses
+// (1.61), all array pointers kept in scalar registers (1.58).
+__global__ __launch_bounds__(ABX* EX_RY, 2) void k_adj_explicit(ExplicitArgs a) {
+  const AdjParams& p = a.p;
+  const uint8_t* __restrict__ type = a.type;
+  const DevPatch* __restrict__ pt = a.pt;
+  // a plane's state (rows b + 1; rows 0 and EX_RY + 1: the rows past the
+  // workgroup's sides), the weights of u, v, w, T, and those of k and omega
+  // with the strain weights of the y differences.  The state and the first
+  // weights alternate between two buffers, so two barriers per plane suffice:
+  // a wave that stages plane m + 1 has passed the second barrier of plane m,
+  // and the buffer it writes was last read before that wave's slowest
+  // companion passed the first barrier of plane m.
+  __shared__ double ls[2][7][EX_RY + 2][ABX];
+  __shared__ double lw[2][4][EX_RY][ABX];
+  __shared__ double lb[5][EX_RY][ABX];
+  __shared__ uint8_t lt[2][EX_RY + 2][ABX];
+  int tx, ty, tz;
+  if (!adj_tile(p, tx, ty, tz)) return;  // (whole workgroup)
+  // (a wave is one row: its index, and with it every row and plane offset,
+  // is kept in scalar registers)
+  const int lane = threadIdx.x, b = __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const int i = tx * ADJ_TX - 2 + lane, j = ty * (EX_RY - 2) - 1 + b;
+  // byte offsets in a dense row and a padded row of types, clamped
+  const unsigned vi = 8u * (unsigned)min(max(i, 0), p.nx - 1);
+  const unsigned vt = (unsigned)(min(max(i, -1), p.nx) + 1);
+  const bool pi = i >= -1 && i <= p.nx, bi = i >= 0 && i < p.nx;
+  const bool d3 = p.d3 != 0;
+  const int k0 = tz * p.cz, k1 = min(p.nz, k0 + p.cz);
+  const bool inner = b >= 1 && b <= (EX_RY - 2);  // rows with results (wave uniform)
+  const bool res = inner && lane >= 2 && lane < 2 + ADJ_TX && bi && j < p.ny;
+  const bool edge = b == 0 || b == EX_RY - 1;
+  const int je = b == 0 ? j - 1 : j + 1, re = b == 0 ? 0 : EX_RY + 1;
+  const size_t plane = (size_t)p.nx * p.ny;
+  // Cell (i, r, m), every load unconditional at indices clamped into the
+  // arrays: past the padded array the type reads as solid, and the values of
+  // a cell that is not fluid are never used.
+  auto load = [&](int r, int m, AdjCell& c) {
+    const int rq = min(max(r, 0), p.ny - 1), mq = min(max(m, 0), p.nz - 1);
+    const size_t D = mq * plane + (size_t)rq * p.nx;
+    const auto io = explicit_io();
+    c.v[0] = *row_at(io->u + D, vi);
+    c.v[1] = *row_at(io->v + D, vi);
+    c.v[2] = *row_at(io->w + D, vi);
+    c.v[3] = *row_at(io->T + D, vi);
+    c.v[4] = *row_at(io->k + D, vi);
+    c.v[5] = *row_at(io->om + D, vi);
+    c.t = adj_type(p, type, vt, pi, r, m);
+    c.nu = 0.0;
+  };
+  auto load_bar = [&](int m, double (&y)[NF]) {
+    const int rq = min(max(j, 0), p.ny - 1), mq = min(max(m, 0), p.nz - 1);
+    const size_t D = mq * plane + (size_t)rq * p.nx;
+    const auto io = explicit_io();
+    y[0] = *row_at(io->ybu + D, vi);
+    y[1] = *row_at(io->ybv + D, vi);
+    y[2] = *row_at(io->ybw + D, vi);
+    y[3] = *row_at(io->ybT + D, vi);
+    y[4] = *row_at(io->ybk + D, vi);
+    y[5] = *row_at(io->ybo + D, vi);
+  };
+  double g0[NF], is[NF];
+  field_coef(p, g0, is);
+  const int m0 = d3 ? k0 - 1 : 0, m1 = d3 ? k1 : 0;  // planes weighed
+  // cc: the plane weighed, cp: the one above, ce: the plane's row past the
+  // side; the plane below stays in the other LDS buffer
+  AdjCell cc, cp, ce;
+  load(j, m0 - 1, cc);
+  cc.v[3] -= p.T_ref;
+  cc.nu = adj_nut(p, cc);
+#pragma unroll
+  for (int f = 0; f < NF; ++f) ls[1][f][b + 1][lane] = cc.v[f];
+  ls[1][6][b + 1][lane] = cc.nu;
+  lt[1][b + 1][lane] = (uint8_t)cc.t;
+  load(j, m0, cc);
+  load(j, m0 + 1, cp);
+  if (edge) load(je, m0, ce);
+  double y[NF];
+  load_bar(m0, y);
+  cc.v[3] -= p.T_ref;
+  cc.nu = adj_nut(p, cc);
+  // the plane below: its weights, strain weights of the z differences,
+  // closure derivatives and partial result
+  double Wp4 = 0, Wp5 = 0, Lzp[3] = {0, 0, 0}, dkp = 0, dwp = 0;
+  AdjAcc ap;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) ap.x[f] = 0.0;
+  ap.nb = ap.pb = 0.0;
+  bool fp = false;  // the cell below is fluid
+  auto store = [&](int m) {
+    if (fp && p.komega) {
       // nu_t is the closure of this cell's k and omega
-      double nt, dk, dw;
-      closure_grad(ph.nu, c.v[4], c.v[5], nt, dk, dw);
-      xb[4] += nb * dk;
-      xb[5] += nb * dw;
+      ap.x[4] += ap.nb * dkp;
+      ap.x[5] += ap.nb * dwp;
     }
+    if (res) {
+      const size_t D = m * plane + (size_t)j * p.nx;
+      const auto io = explicit_io();
+      *row_at(io->xu + D, vi) = ap.x[0];
+      *row_at(io->xv + D, vi) = ap.x[1];
+      *row_at(io->xw + D, vi) = ap.x[2];
+      *row_at(io->xp + D, vi) = ap.pb;
+      *row_at(io->xT + D, vi) = ap.x[3];
+      *row_at(io->xk + D, vi) = ap.x[4];
+      *row_at(io->xo + D, vi) = ap.x[5];
+    }
+  };
+  for (int m = m0, buf = 0; m <= m1; ++m, buf ^= 1) {
+    const bool fc = is_fluid((uint8_t)cc.t);
+    // ---- stage the plane
+#pragma unroll
+    for (int f = 0; f < NF; ++f) ls[buf][f][b + 1][lane] = cc.v[f];
+    ls[buf][6][b + 1][lane] = cc.nu;
+    lt[buf][b + 1][lane] = (uint8_t)cc.t;
+    if (edge) {
+      ce.v[3] -= p.T_ref;
+      ce.nu = adj_nut(p, ce);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) ls[buf][f][re][lane] = ce.v[f];
+      ls[buf][6][re][lane] = ce.nu;
+      lt[buf][re][lane] = (uint8_t)ce.t;
+    }
+    double W[NF];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) W[a] = fc && (a < 2 || d3) ? p.dt * y[a] : 0.0;
+    W[3] = fc && p.energy ? p.dt * y[3] : 0.0;
+    W[4] = W[5] = 0.0;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) lw[buf][f][b][lane] = W[f];
+    __syncthreads();
+    cp.v[3] -= p.T_ref;
+    cp.nu = adj_nut(p, cp);
+    const int tzl = lt[buf ^ 1][b + 1][lane];
+    // ---- weights of this plane's outputs
+    AdjCell xl, xh;  // the x neighbours
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      xl.v[f] = lane_below(cc.v[f]);
+      xh.v[f] = lane_above(cc.v[f]);
+    }
+    xl.nu = lane_below(cc.nu);
+    xh.nu = lane_above(cc.nu);
+    xl.t = lane_below(cc.t);
+    xh.t = lane_above(cc.t);
+    const int tyl = lt[buf][b][lane], tyh = lt[buf][b + 2][lane];
+    AdjAcc A;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) A.x[f] = y[f];
+    A.nb = A.pb = 0.0;
+    double L4[6] = {0, 0, 0, 0, 0, 0}, dkc = 0.0, dwc = 0.0;  // S00 S11 S22 S01 S02 S12
+    if (fc && p.komega) {
+      double rk = 0.0, rw = 0.0;
+      double G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          if (d == 2 && !d3) continue;
+          double nv[3], nk, nw, nn;  // velocity, k, omega, nu_t across the face
+          int tn;
+          if (d == 1 || (d == 2 && s == 0)) {
+            const int r = d == 2 ? b + 1 : (s ? b + 2 : b), bf = d == 2 ? buf ^ 1 : buf;
+            nv[0] = ls[bf][0][r][lane];
+            nv[1] = ls[bf][1][r][lane];
+            nv[2] = ls[bf][2][r][lane];
+            nk = ls[bf][4][r][lane];
+            nw = ls[bf][5][r][lane];
+            nn = ls[bf][6][r][lane];
+            tn = d == 2 ? tzl : (s ? tyh : tyl);
+          } else {
+            const AdjCell& q = d == 0 ? (s ? xh : xl) : cp;
+            nv[0] = q.v[0];
+            nv[1] = q.v[1];
+            nv[2] = q.v[2];
+            nk = q.v[4];
+            nw = q.v[5];
+            nn = q.nu;
+            tn = q.t;
+          }
+          if (!is_fluid((uint8_t)tn)) {
+            const DevPatch& pp = pt[tn & 0x7f];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) nv[a] = ghost<double>(pp, G_U + a, cc.v[a], p.komega);
+            nk = ghost<double>(pp, G_K, cc.v[4], p.komega);
+            nw = ghost<double>(pp, G_OM, cc.v[5], p.komega);
+            nn = ghost<double>(pp, G_NUT, cc.nu, p.komega);
+          }
+          const double sg = s ? 1.0 : -1.0;
+          const double Uf = 0.5 * (cc.v[d] + nv[d]);
+          const double nutf = 0.5 * (cc.nu + nn);
+          const bool own = (Uf >= 0.0) == (s == 1);
+          rk += p.ih[d] * (-sg * Uf * (own ? cc.v[4] : nk) +
+                           (p.nu + nutf * p.is4) * (nk - cc.v[4]) * p.ih[d]);
+          rw += p.ih[d] * (-sg * Uf * (own ? cc.v[5] : nw) +
+                           (p.nu + nutf * p.is5) * (nw - cc.v[5]) * p.ih[d]);
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+            if (a < 2 || d3) G[a][d] += sg * p.ih2[d] * nv[a];
+        }
+      const double S[6] = {G[0][0],
+                           G[1][1],
+                           G[2][2],
+                           0.5 * (G[0][1] + G[1][0]),
+                           0.5 * (G[0][2] + G[2][0]),
+                           0.5 * (G[1][2] + G[2][1])};
+      const double S2 = 2.0 * (S[0] * S[0] + S[1] * S[1] + S[2] * S[2] +
+                               2.0 * (S[3] * S[3] + S[4] * S[4] + S[5] * S[5]));
+      AdjClosure q;
+      adj_closure(p, cc.v[4], cc.v[5], q);
+      dkc = q.dk;
+      dwc = q.dw;
+      const double kn = cc.v[4] + p.dt * (rk + cc.nu * S2);
+      const double wn = cc.v[5] + p.dt * (rw + q.al * S2);
+      const bool pk = kn > C_EPS;
+      const bool fixed = (cc.t & FIXED_BIT) != 0;
+      const bool pw = fixed || wn > C_EPS;
+      W[4] = pk ? p.dt * y[4] : 0.0;
+      W[5] = (!fixed && pw) ? p.dt * y[5] : 0.0;
+      A.x[4] = pk ? y[4] : 0.0;
+      A.x[5] = pw ? y[5] : 0.0;
+      const double lam4 = 4.0 * (W[4] * cc.nu + W[5] * q.al);
+#pragma unroll
+      for (int r = 0; r < 6; ++r) L4[r] = lam4 * S[r];
+      // production nu_t S^2 and alpha S^2 at this cell
+      A.nb = W[4] * S2;
+      A.x[4] += W[5] * S2 * q.ak;
+      A.x[5] += W[5] * S2 * q.aw;
+    }
+    lb[0][b][lane] = W[4];
+    lb[1][b][lane] = W[5];
+    lb[2][b][lane] = L4[3];
+    lb[3][b][lane] = L4[1];
+    lb[4][b][lane] = L4[5];
+    __syncthreads();
+    // loads of the next plane weighed (its upper neighbour, adjoints and the
+    // row past the side), used after the next barriers
+    AdjCell cn;
+    double yn[NF];
+    load(j, m + 2, cn);
+    load_bar(m + 1, yn);
+    if (edge) load(je, m + 1, ce);
+    if (inner) {
+      // ---- the face and the strain rates between the plane below and this one
+      if (d3 && m > k0 - 1) {
+        if (fp && fc) {
+          double nv[NF], Wn[NF];
+#pragma unroll
+          for (int f = 0; f < NF; ++f) nv[f] = ls[buf ^ 1][f][b + 1][lane];
+#pragma unroll
+          for (int f = 0; f < 4; ++f) Wn[f] = lw[buf ^ 1][f][b][lane];
+          Wn[4] = Wp4;
+          Wn[5] = Wp5;
+          face_adj<2>(p, nv, ls[buf ^ 1][6][b + 1][lane], Wn, cc.v, cc.nu, W, ap, A);
+        }
+        if (fp) {
+          ap.x[0] -= L4[4] * p.ih2[2];
+          ap.x[1] -= L4[5] * p.ih2[2];
+          ap.x[2] -= L4[2] * p.ih2[2];
+        }
+        if (fc) {
+          A.x[0] += Lzp[0] * p.ih2[2];
+          A.x[1] += Lzp[1] * p.ih2[2];
+          A.x[2] += Lzp[2] * p.ih2[2];
+        }
+        if (m > k0) store(m - 1);
+      }
+      // ---- within the plane
+      if (m >= k0 && m < k1) {
+        // x faces: each lane takes its lower face and hands the lower cell's
+        // part to the lane below
+        {
+          double Wl[NF];
+#pragma unroll
+          for (int f = 0; f < NF; ++f) Wl[f] = lane_below(W[f]);
+          AdjAcc lo;
+#pragma unroll
+          for (int f = 0; f < NF; ++f) lo.x[f] = 0.0;
+          lo.nb = lo.pb = 0.0;
+          if (fc && is_fluid((uint8_t)xl.t))
+            face_adj<0>(p, xl.v, xl.nu, Wl, cc.v, cc.nu, W, lo, A);
+#pragma unroll
+          for (int f = 0; f < NF; ++f) A.x[f] += lane_above(lo.x[f]);
+          A.nb += lane_above(lo.nb);
+          A.pb += lane_above(lo.pb);
+        }
+        // strain rates of the x neighbours (0 where they are not fluid)
+        const double sx0 = lane_below(L4[0]) - lane_above(L4[0]);
+        const double sx1 = lane_below(L4[3]) - lane_above(L4[3]);
+        const double sx2 = lane_below(L4[4]) - lane_above(L4[4]);
+        if (fc) {
+          A.x[0] += sx0 * p.ih2[0];
+          A.x[1] += sx1 * p.ih2[0];
+          A.x[2] += sx2 * p.ih2[0];
+          // y faces and the y neighbours' strain rates
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const int r = s ? b + 2 : b, q = s ? b + 1 : b - 1;
+            if (is_fluid((uint8_t)(s ? tyh : tyl))) {
+              double nv[NF], Wn[NF];
+#pragma unroll
+              for (int f = 0; f < NF; ++f) nv[f] = ls[buf][f][r][lane];
+              const double nn = ls[buf][6][r][lane];
+#pragma unroll
+              for (int f = 0; f < 4; ++f) Wn[f] = lw[buf][f][q][lane];
+              Wn[4] = lb[0][q][lane];
+              Wn[5] = lb[1][q][lane];
+              AdjAcc other;
+#pragma unroll
+              for (int f = 0; f < NF; ++f) other.x[f] = 0.0;
+              other.nb = other.pb = 0.0;
+              if (s)
+                face_adj<1>(p, cc.v, cc.nu, W, nv, nn, Wn, A, other);
+              else
+                face_adj<1>(p, nv, nn, Wn, cc.v, cc.nu, W, other, A);
+              const double f2 = s ? -p.ih2[1] : p.ih2[1];
+              A.x[0] += lb[2][q][lane] * f2;
+              A.x[1] += lb[3][q][lane] * f2;
+              A.x[2] += lb[4][q][lane] * f2;
+            }
+          }
+          // boundary faces
+          unsigned gm = (!is_fluid((uint8_t)xl.t) ? 1u : 0u) | (!is_fluid((uint8_t)xh.t) ? 2u : 0u) |
+                        (!is_fluid((uint8_t)tyl) ? 4u : 0u) | (!is_fluid((uint8_t)tyh) ? 8u : 0u);
+          if (d3)
+            gm |= (!is_fluid((uint8_t)tzl) ? 16u : 0u) | (!is_fluid((uint8_t)cp.t) ? 32u : 0u);
+          while (gm) {
+            const int q = __ffs(gm) - 1;
+            gm &= gm - 1;
+            const int d = q >> 1, s = q & 1;
+            const int tn = q == 0 ? xl.t : (q == 1 ? xh.t : (q == 2 ? tyl : (q == 3 ? tyh : (q == 4 ? tzl : cp.t))));
+            const double lam[3] = {d == 0 ? L4[0] : (d == 1 ? L4[3] : L4[4]),
+                                   d == 0 ? L4[3] : (d == 1 ? L4[1] : L4[5]),
+                                   d == 0 ? L4[4] : (d == 1 ? L4[5] : L4[2])};
+            ghost_face_adj(p, pt[tn & 0x7f], d, s, cc, W, lam, A);
+          }
+          // buoyancy -beta_T theta g_a
+          if (p.buoyancy) A.x[3] += W[0] * p.bg[0] + W[1] * p.bg[1] + W[2] * p.bg[2];
+        }
+      }
+    }
+    // ---- this plane becomes the one below
+    Wp4 = W[4];
+    Wp5 = W[5];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) y[f] = yn[f];
+    Lzp[0] = L4[4];
+    Lzp[1] = L4[5];
+    Lzp[2] = L4[2];
+    dkp = dkc;
+    dwp = dwc;
+    ap = A;
+    fp = fc;
+    cc = cp;
+    cp = cn;
   }
-  xu[D] = xb[0];
-  xv[D] = xb[1];
-  xw[D] = xb[2];
-  xp[D] = pb;
-  xT[D] = xb[3];
-  xk[D] = xb[4];
-  xo[D] = xb[5];
+  if (!d3 && inner) store(0);
 }
 
 void launch_explicit_adjoint(const Geom& g, const Phys& ph, const uint8_t* type,
-                             const DevPatch* pt, const double* const st[7],
-                             const double* const yb[6], double* W, double* pass, double* L4S,
-                             double* nu, double* const xb[7], hipStream_t s) {
-  const AdjState S{st[0], st[1], st[2], st[4], st[5], st[6], nu};
-  const dim3 G = adj_grid(g), B(ABX, ABY);
-  if (ph.komega) hipLaunchKernelGGL(k_adj_nut, G, B, 0, s, g, ph, type, st[5], st[6], nu);
-  hipLaunchKernelGGL(k_adj_ex_weights, G, B, 0, s, g, ph, type, pt, S, yb[0], yb[1], yb[2],
-                     yb[3], yb[4], yb[5], W, pass, L4S);
-  hipLaunchKernelGGL(k_adj_ex_gather, G, B, 0, s, g, ph, type, pt, S, yb[0], yb[1], yb[2],
-                     yb[3], yb[4], yb[5], W, pass, L4S, xb[0], xb[1], xb[2], xb[3], xb[4],
-                     xb[5], xb[6]);
+                             const DevPatch* pt, const double* const st[6],
+                             const double* const yb[6], double* const xb[7], hipStream_t s) {
+  const ExplicitArgs a{{st[0], st[1], st[2], st[3], st[4], st[5], yb[0], yb[1], yb[2], yb[3],
+                        yb[4], yb[5], xb[0], xb[1], xb[2], xb[3], xb[4], xb[5], xb[6]},
+                       adj_params(g, ph, EX_RY),
+                       type,
+                       pt};
+  hipLaunchKernelGGL(k_adj_explicit, adj_grid(a.p), dim3(ABX, EX_RY), 0, s, a);
 }
 
 // ---- destruction step (Sec. 2.5, Algorithm 3, eqs. k_des_step, o_des_step,
@@ -484,13 +738,12 @@ void launch_explicit_adjoint(const Geom& g, const Phys& ph, const uint8_t* type,
 // f_beta(chi_omega) omega, chi_omega = |X| / (beta*_inf omega-hat)^3 with X
 // the vortex stretching a^T S a - |a|^2 tr S (a the axial vector of the
 // antisymmetric part of the velocity gradient, S its symmetric part); fixed
-// cells keep omega, non-fluid cells keep both.  Pass 1 stores per output cell
-// the adjoints of its gradients: of grad k and grad omega (E, six values) and
-// of the velocity gradient G (M, nine values); pass 2 gathers, per input
-// cell, its own terms and those of the gradients that read it.
+// cells keep omega, non-fluid cells keep both.  The weights of an output cell
+// are the adjoints of its gradients: of grad k and grad omega (E, six values)
+// and of the velocity gradient G (M, nine values); an input cell gathers its
+// own terms and those of the gradients that read it.
 namespace {
 struct DesLocal {
-  double kn, wn;           // outputs
   double dkn_k, dkn_w;     // d k' / d (own k, own omega), gradients held
   double dwn_w;            // d omega' / d own omega, gradient held
   double lam_k;            // d k' / d (grad k . grad omega)
@@ -498,9 +751,9 @@ struct DesLocal {
 };
 
 // The destruction at one fluid cell from its k, omega, the gradients of k
-// and omega and the velocity gradient, with the partial derivatives the
-// reverse mode needs.
-__device__ __forceinline__ DesLocal des_local(const Phys& ph, double tau, double kP, double wP,
+// and omega and the velocity gradient: the partial derivatives the reverse
+// mode needs.
+__device__ __forceinline__ DesLocal des_local(double inu, double tau, double kP, double wP,
                                               const double (&gk)[3], const double (&gw)[3],
                                               const double (&G)[3][3], bool fixed) {
   DesLocal r;
@@ -509,24 +762,23 @@ __device__ __forceinline__ DesLocal des_local(const Phys& ph, double tau, double
   const double ioh = 1.0 / oh, ioh3 = ioh * ioh * ioh;
   const double dkdw = gk[0] * gw[0] + gk[1] * gw[1] + gk[2] * gw[2];
   const double chik = dkdw * ioh3;
-  const double q = 1.0 + 400.0 * chik * chik;
-  const double fbs = chik <= 0.0 ? 1.0 : (1.0 + 680.0 * chik * chik) / q;
-  const double dfbs = chik <= 0.0 ? 0.0 : 560.0 * chik / (q * q);  // d fbs / d chi_k
-  const double ret = kP * ioh / ph.nu;
+  const double iq = 1.0 / (1.0 + 400.0 * chik * chik);
+  const double fbs = chik <= 0.0 ? 1.0 : (1.0 + 680.0 * chik * chik) * iq;
+  const double dfbs = chik <= 0.0 ? 0.0 : 560.0 * chik * iq * iq;  // d fbs / d chi_k
+  const double ret = kP * ioh * inu;
   const double x = ret * (1.0 / C_R_BETA);
   const double x4 = x * x * x * x;
-  const double bst = C_BSTAR * (1.0 - (11.0 / 15.0) / (1.0 + x4));
-  const double dbst = C_BSTAR * (11.0 / 15.0) / ((1.0 + x4) * (1.0 + x4)) * 4.0 * x * x * x *
+  const double i4 = 1.0 / (1.0 + x4);
+  const double bst = C_BSTAR * (1.0 - (11.0 / 15.0) * i4);
+  const double dbst = C_BSTAR * (11.0 / 15.0) * i4 * i4 * 4.0 * x * x * x *
                       (1.0 / C_R_BETA);  // d bst / d ret
-  const double Dk = 1.0 + tau * bst * fbs * wP;
-  r.kn = kP / Dk;
-  const double dDk = -kP / (Dk * Dk);  // d k' / d Dk
-  const double dret_k = ioh / ph.nu, dret_w = live ? -ret * ioh : 0.0;
+  const double iDk = 1.0 / (1.0 + tau * bst * fbs * wP);
+  const double dDk = -kP * iDk * iDk;  // d k' / d Dk
+  const double dret_k = ioh * inu, dret_w = live ? -ret * ioh : 0.0;
   const double dchik_w = live ? -3.0 * chik * ioh : 0.0;
-  r.dkn_k = 1.0 / Dk + dDk * tau * fbs * wP * dbst * dret_k;
+  r.dkn_k = iDk + dDk * tau * fbs * wP * dbst * dret_k;
   r.dkn_w = dDk * tau * (bst * fbs + fbs * wP * dbst * dret_w + bst * wP * dfbs * dchik_w);
   r.lam_k = dDk * tau * bst * wP * dfbs * ioh3;
-  r.wn = wP;
   r.dwn_w = 1.0;
   r.lam_w = 0.0;
   if (!fixed) {
@@ -539,12 +791,12 @@ __device__ __forceinline__ DesLocal des_local(const Phys& ph, double tau, double
     const double X = aSa - (a0 * a0 + a1 * a1 + a2 * a2) * (G[0][0] + G[1][1] + G[2][2]);
     const double c3 = 1.0 / (C_BSTAR * C_BSTAR * C_BSTAR);
     const double chiw = fabs(X) * ioh3 * c3;
-    const double fb = (1.0 + 70.0 * chiw) / (1.0 + 80.0 * chiw);
-    const double dfb = -10.0 / ((1.0 + 80.0 * chiw) * (1.0 + 80.0 * chiw));
-    const double Dw = 1.0 + tau * C_BETA_I * fb * wP;
-    r.wn = wP / Dw;
-    const double dfbw = -tau * C_BETA_I * wP * wP / (Dw * Dw);  // d omega' / d fb
-    r.dwn_w = 1.0 / (Dw * Dw) + dfbw * dfb * (live ? -3.0 * chiw * ioh : 0.0);
+    const double i8 = 1.0 / (1.0 + 80.0 * chiw);
+    const double fb = (1.0 + 70.0 * chiw) * i8;
+    const double dfb = -10.0 * i8 * i8;
+    const double iDw = 1.0 / (1.0 + tau * C_BETA_I * fb * wP);
+    const double dfbw = -tau * C_BETA_I * wP * wP * iDw * iDw;  // d omega' / d fb
+    r.dwn_w = iDw * iDw + dfbw * dfb * (live ? -3.0 * chiw * ioh : 0.0);
     const double sgn = X > 0.0 ? 1.0 : (X < 0.0 ? -1.0 : 0.0);
     r.lam_w = dfbw * dfb * sgn * ioh3 * c3;
   }
@@ -574,147 +826,253 @@ __device__ __forceinline__ void stretch_grad(const double (&G)[3][3], double (&d
   dX[0][1] -= 0.5 * ga[2];
 }
 
-struct DesState {
-  const double *u, *v, *w, *k, *om;  // padded
-};
-
-// gradients of k, omega and the velocity at fluid cell P, ghosts substituted
-__device__ __forceinline__ void des_gradients(const Geom& g, const Phys& ph, const DesState& S,
-                                              const uint8_t* type, const DevPatch* pt, int P,
-                                              double (&gk)[3], double (&gw)[3],
-                                              double (&G)[3][3]) {
-  const int st[3] = {1, g.sx, g.sxy};
-  const double ih2[3] = {0.5 / g.hx, 0.5 / g.hy, 0.5 / g.hz};
-  const double own[5] = {S.u[P], S.v[P], S.w[P], S.k[P], S.om[P]};
-  const int code[5] = {G_U, G_V, G_W, G_K, G_OM};
-  for (int d = 0; d < 3; ++d) {
-    gk[d] = gw[d] = 0.0;
-    for (int a = 0; a < 3; ++a) G[a][d] = 0.0;
-  }
-  for (int d = 0; d < g.dim; ++d) {
-    double val[2][5];
-    for (int s = 0; s < 2; ++s) {
-      const int Q = P + (s ? 1 : -1) * st[d];
-      const uint8_t tq = type[Q];
-      if (is_fluid(tq)) {
-        val[s][0] = S.u[Q];
-        val[s][1] = S.v[Q];
-        val[s][2] = S.w[Q];
-        val[s][3] = S.k[Q];
-        val[s][4] = S.om[Q];
-      } else {
-        const DevPatch& pp = pt[tq & 0x7f];
-        for (int f = 0; f < 5; ++f) val[s][f] = ghost<double>(pp, code[f], own[f], ph.komega);
-      }
-    }
-    for (int a = 0; a < g.dim; ++a) G[a][d] = (val[1][a] - val[0][a]) * ih2[d];
-    gk[d] = (val[1][3] - val[0][3]) * ih2[d];
-    gw[d] = (val[1][4] - val[0][4]) * ih2[d];
-  }
+constexpr int ND = 5;  // u v w k omega
+__device__ __forceinline__ int des_code(int f) {
+  return f < 3 ? G_U + f : (f == 3 ? G_K : G_OM);
 }
+struct DesIo {
+  const double* s[ND];        // state u v w k omega, dense
+  const double *kb, *wb;      // adjoints of k' and omega', dense
+  double* x[ND];              // adjoints of the inputs, dense
+};
+struct DesCell {
+  double v[ND];
+  int t;
+};
 }  // namespace
 
-// Pass 1: E (6 padded arrays: d k'/d grad k, d k'/d grad omega, times kbar)
-// and M (9: d omega'/d G times wbar) per output cell.
-__global__ __launch_bounds__(ABX* ABY) void k_adj_des_weights(
-    Geom g, Phys ph, const uint8_t* __restrict__ type, const DevPatch* __restrict__ pt,
-    DesState S, double tau, const double* __restrict__ kb, const double* __restrict__ wb,
-    double* __restrict__ E, double* __restrict__ M) {
-  int i, j, k;
-  if (!adj_cell(g, i, j, k)) return;
-  const int P = g.idx(i, j, k);
-  const size_t D = ((size_t)k * g.ny + j) * g.nx + i;
-  const size_t T = (size_t)g.total;
-  const uint8_t tp = type[P];
-  // formed in registers and stored once (zero where the cell is not fluid)
-  double Ev[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  double Mv[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  if (is_fluid(tp)) {
-    double gk[3], gw[3], G[3][3];
-    des_gradients(g, ph, S, type, pt, P, gk, gw, G);
-    const DesLocal r = des_local(ph, tau, S.k[P], S.om[P], gk, gw, G, (tp & FIXED_BIT) != 0);
-    const double lk = kb[D] * r.lam_k;
-    #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      Ev[d] = lk * gw[d];
-      Ev[3 + d] = lk * gk[d];
+// The destruction step's reverse mode: 97 bytes per cell (it was 474 with the
+// fifteen weights of every cell stored and gathered).  Bound by FP64 issue and
+// latency at three waves per SIMD: 0.78 ms per call on the 512 x 256 x 128
+// room, from 2.71 ms for the two passes.  Four waves per SIMD (128 VGPRs)
+// spill 130 registers: 2.16 ms.
+__global__ __launch_bounds__(ABX* DS_RY, 3) void k_adj_destroy(AdjParams p,
+                                                            const uint8_t* __restrict__ type,
+                                                            const DevPatch* __restrict__ pt,
+                                                            double tau, DesIo io) {
+  // a plane's state (rows b + 1; rows 0 and DS_RY + 1: the rows past the
+  // workgroup's sides) and the weights of its y differences.  The state
+  // alternates between two buffers, the other one holding the plane below.
+  // It is read between the two barriers of a plane and the weights after the
+  // second, so each is overwritten only after a barrier that follows its
+  // last reader.
+  __shared__ double ls[2][ND][DS_RY + 2][ABX];
+  __shared__ double ly[ND][DS_RY][ABX];
+  __shared__ uint8_t lt[2][DS_RY + 2][ABX];
+  int tx, ty, tz;
+  if (!adj_tile(p, tx, ty, tz)) return;  // (whole workgroup)
+  const int lane = threadIdx.x, b = __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const int i = tx * ADJ_TX - 2 + lane, j = ty * (DS_RY - 2) - 1 + b;
+  // byte offsets in a dense row and a padded row of types, clamped
+  const unsigned vi = 8u * (unsigned)min(max(i, 0), p.nx - 1);
+  const unsigned vt = (unsigned)(min(max(i, -1), p.nx) + 1);
+  const bool pi = i >= -1 && i <= p.nx, bi = i >= 0 && i < p.nx;
+  const bool d3 = p.d3 != 0;
+  const int k0 = tz * p.cz, k1 = min(p.nz, k0 + p.cz);
+  const bool inner = b >= 1 && b <= (DS_RY - 2);  // rows with results (wave uniform)
+  const bool res = inner && lane >= 2 && lane < 2 + ADJ_TX && bi && j < p.ny;
+  const bool edge = b == 0 || b == DS_RY - 1;
+  const int je = b == 0 ? j - 1 : j + 1, re = b == 0 ? 0 : DS_RY + 1;
+  const size_t plane = (size_t)p.nx * p.ny;
+  // (loads as in k_adj_explicit)
+  auto load = [&](int r, int m, DesCell& c) {
+    const int rq = min(max(r, 0), p.ny - 1), mq = min(max(m, 0), p.nz - 1);
+    const size_t D = mq * plane + (size_t)rq * p.nx;
+#pragma unroll
+    for (int f = 0; f < ND; ++f) c.v[f] = *row_at(io.s[f] + D, vi);
+    c.t = adj_type(p, type, vt, pi, r, m);
+  };
+  const int m0 = d3 ? k0 - 1 : 0, m1 = d3 ? k1 : 0;  // planes weighed
+  // cc: the plane weighed, cp: the one above, ce: the plane's row past the
+  // side; the plane below stays in the other LDS buffer
+  DesCell cc, cp, ce;
+  load(j, m0 - 1, cc);
+#pragma unroll
+  for (int f = 0; f < ND; ++f) ls[1][f][b + 1][lane] = cc.v[f];
+  lt[1][b + 1][lane] = (uint8_t)cc.t;
+  load(j, m0, cc);
+  load(j, m0 + 1, cp);
+  if (edge) load(je, m0, ce);
+  double kb, wb;
+  auto load_bar = [&](int m, double& a, double& c) {
+    const int rq = min(max(j, 0), p.ny - 1), mq = min(max(m, 0), p.nz - 1);
+    const size_t D = mq * plane + (size_t)rq * p.nx;
+    a = *row_at(io.kb + D, vi);
+    c = *row_at(io.wb + D, vi);
+  };
+  load_bar(m0, kb, wb);
+  // the plane below: partial result and weights of its z differences
+  double xp[ND] = {0, 0, 0, 0, 0}, zp[ND] = {0, 0, 0, 0, 0};
+  bool fp = false;
+  auto store = [&](int m) {
+    const size_t D = m * plane + (size_t)j * p.nx;
+    if (res)
+#pragma unroll
+      for (int f = 0; f < ND; ++f) *row_at(io.x[f] + D, vi) = xp[f];
+  };
+  for (int m = m0, buf = 0; m <= m1; ++m, buf ^= 1) {
+    const bool fc = is_fluid((uint8_t)cc.t);
+#pragma unroll
+    for (int f = 0; f < ND; ++f) ls[buf][f][b + 1][lane] = cc.v[f];
+    lt[buf][b + 1][lane] = (uint8_t)cc.t;
+    if (edge) {
+#pragma unroll
+      for (int f = 0; f < ND; ++f) ls[buf][f][re][lane] = ce.v[f];
+      lt[buf][re][lane] = (uint8_t)ce.t;
     }
-    if (r.lam_w != 0.0) {
-      double dX[3][3];
-      stretch_grad(G, dX);
-      const double lw = wb[D] * r.lam_w;
-      #pragma unroll
-      for (int p = 0; p < 3; ++p)
-        #pragma unroll
-        for (int q = 0; q < 3; ++q) Mv[3 * p + q] = lw * dX[p][q];
+    __syncthreads();
+    const int tzl = lt[buf ^ 1][b + 1][lane];
+    // ---- weights of this plane's outputs
+    DesCell xl, xh;
+#pragma unroll
+    for (int f = 0; f < ND; ++f) {
+      xl.v[f] = lane_below(cc.v[f]);
+      xh.v[f] = lane_above(cc.v[f]);
     }
-  }
-  #pragma unroll
-  for (int q = 0; q < 6; ++q) E[q * T + P] = Ev[q];
-  #pragma unroll
-  for (int q = 0; q < 9; ++q) M[q * T + P] = Mv[q];
-}
-
-// Pass 2: the adjoints of the inputs u, v, w, k, omega (dense).
-__global__ __launch_bounds__(ABX* ABY) void k_adj_des_gather(
-    Geom g, Phys ph, const uint8_t* __restrict__ type, const DevPatch* __restrict__ pt,
-    DesState S, double tau, const double* __restrict__ kb, const double* __restrict__ wb,
-    const double* __restrict__ E, const double* __restrict__ M, double* __restrict__ xu,
-    double* __restrict__ xv, double* __restrict__ xw, double* __restrict__ xk,
-    double* __restrict__ xo) {
-  int i, j, k;
-  if (!adj_cell(g, i, j, k)) return;
-  const int P = g.idx(i, j, k);
-  const size_t D = ((size_t)k * g.ny + j) * g.nx + i;
-  const size_t T = (size_t)g.total;
-  const uint8_t tp = type[P];
-  double x[5] = {0.0, 0.0, 0.0, kb[D], wb[D]};  // u v w k omega
-  if (is_fluid(tp)) {
-    double gk[3], gw[3], G[3][3];
-    des_gradients(g, ph, S, type, pt, P, gk, gw, G);
-    const DesLocal r = des_local(ph, tau, S.k[P], S.om[P], gk, gw, G, (tp & FIXED_BIT) != 0);
-    x[3] = kb[D] * r.dkn_k;
-    x[4] = kb[D] * r.dkn_w + wb[D] * r.dwn_w;
-    const int st[3] = {1, g.sx, g.sxy};
-    const double ih2[3] = {0.5 / g.hx, 0.5 / g.hy, 0.5 / g.hz};
-    for (int b = 0; b < g.dim; ++b)
-      for (int s = 0; s < 2; ++s) {
-        const double sg = s ? 1.0 : -1.0;
-        const int Q = P + (s ? 1 : -1) * st[b];
-        const uint8_t tq = type[Q];
-        if (is_fluid(tq)) {
-          // this cell is Q's neighbour on Q's side -sg along b
-          const double f = -sg * ih2[b];
-          x[3] += E[b * T + Q] * f;
-          x[4] += E[(3 + b) * T + Q] * f;
-          for (int a = 0; a < g.dim; ++a) x[a] += M[(3 * a + b) * T + Q] * f;
-        } else {
-          // this cell's own gradients read it through the ghost
-          const DevPatch& pp = pt[tq & 0x7f];
-          const double f = sg * ih2[b];
-          x[3] += E[b * T + P] * f * slope(pp, G_K, ph.komega);
-          x[4] += E[(3 + b) * T + P] * f * slope(pp, G_OM, ph.komega);
-          for (int a = 0; a < g.dim; ++a)
-            x[a] += M[(3 * a + b) * T + P] * f * slope(pp, G_U + a, ph.komega);
+    xl.t = lane_below(cc.t);
+    xh.t = lane_above(cc.t);
+    const int tyl = lt[buf][b][lane], tyh = lt[buf][b + 2][lane];
+    double x[ND] = {0.0, 0.0, 0.0, kb, wb};
+    // weights by direction of the difference: u, v, w (M), k, omega (E)
+    double wx[ND] = {0, 0, 0, 0, 0}, wy[ND] = {0, 0, 0, 0, 0}, wz[ND] = {0, 0, 0, 0, 0};
+    if (fc) {
+      double gk[3] = {0, 0, 0}, gw[3] = {0, 0, 0};
+      double G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        if (d == 2 && !d3) continue;
+        double n[2][ND];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          int tn;
+          if (d == 1 || (d == 2 && s == 0)) {
+            const int r = d == 2 ? b + 1 : (s ? b + 2 : b), bf = d == 2 ? buf ^ 1 : buf;
+#pragma unroll
+            for (int f = 0; f < ND; ++f) n[s][f] = ls[bf][f][r][lane];
+            tn = d == 2 ? tzl : (s ? tyh : tyl);
+          } else {
+            const DesCell& q = d == 0 ? (s ? xh : xl) : cp;
+#pragma unroll
+            for (int f = 0; f < ND; ++f) n[s][f] = q.v[f];
+            tn = q.t;
+          }
+          if (!is_fluid((uint8_t)tn)) {
+            const DevPatch& pp = pt[tn & 0x7f];
+#pragma unroll
+            for (int f = 0; f < ND; ++f)
+              n[s][f] = ghost<double>(pp, des_code(f), cc.v[f], p.komega);
+          }
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+          if (a < 2 || d3) G[a][d] = (n[1][a] - n[0][a]) * p.ih2[d];
+        gk[d] = (n[1][3] - n[0][3]) * p.ih2[d];
+        gw[d] = (n[1][4] - n[0][4]) * p.ih2[d];
+      }
+      const DesLocal r =
+          des_local(p.inu, tau, cc.v[3], cc.v[4], gk, gw, G, (cc.t & FIXED_BIT) != 0);
+      x[3] = kb * r.dkn_k;
+      x[4] = kb * r.dkn_w + wb * r.dwn_w;
+      const double lk = kb * r.lam_k;
+      wx[3] = lk * gw[0];
+      wy[3] = lk * gw[1];
+      wz[3] = lk * gw[2];
+      wx[4] = lk * gk[0];
+      wy[4] = lk * gk[1];
+      wz[4] = lk * gk[2];
+      if (r.lam_w != 0.0) {
+        double dX[3][3];
+        stretch_grad(G, dX);
+        const double lw = wb * r.lam_w;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          if (a == 2 && !d3) continue;
+          wx[a] = lw * dX[a][0];
+          wy[a] = lw * dX[a][1];
+          wz[a] = lw * dX[a][2];
         }
       }
+    }
+#pragma unroll
+    for (int f = 0; f < ND; ++f) ly[f][b][lane] = wy[f];
+    __syncthreads();
+    // loads of the next plane weighed (its upper neighbour, adjoints and the
+    // row past the side), used after the next barrier
+    DesCell cn;
+    double kbn, wbn;
+    load(j, m + 2, cn);
+    load_bar(m + 1, kbn, wbn);
+    if (edge) load(je, m + 1, ce);
+    if (inner) {
+      if (d3 && m > k0) {
+        // the cell below reads this plane's differences
+        if (fp)
+#pragma unroll
+          for (int f = 0; f < ND; ++f) xp[f] -= wz[f] * p.ih2[2];
+        store(m - 1);
+      }
+      if (m >= k0 && m < k1) {
+        // (every neighbour that is not fluid has weight 0)
+        double gx[ND];
+#pragma unroll
+        for (int f = 0; f < ND; ++f)
+          gx[f] = (lane_below(wx[f]) - lane_above(wx[f])) * p.ih2[0];
+        if (fc) {
+#pragma unroll
+          for (int f = 0; f < ND; ++f) {
+            x[f] += gx[f];
+            x[f] += (ly[f][b - 1][lane] - ly[f][b + 1][lane]) * p.ih2[1];
+            if (d3) x[f] += zp[f] * p.ih2[2];
+          }
+          // this cell's own gradients read it through the ghosts
+          unsigned gm = (!is_fluid((uint8_t)xl.t) ? 1u : 0u) | (!is_fluid((uint8_t)xh.t) ? 2u : 0u) |
+                        (!is_fluid((uint8_t)tyl) ? 4u : 0u) | (!is_fluid((uint8_t)tyh) ? 8u : 0u);
+          if (d3)
+            gm |= (!is_fluid((uint8_t)tzl) ? 16u : 0u) | (!is_fluid((uint8_t)cp.t) ? 32u : 0u);
+          while (gm) {
+            const int q = __ffs(gm) - 1;
+            gm &= gm - 1;
+            const int d = q >> 1;
+            const int tn = q == 0 ? xl.t : (q == 1 ? xh.t : (q == 2 ? tyl : (q == 3 ? tyh : (q == 4 ? tzl : cp.t))));
+            const DevPatch& pp = pt[tn & 0x7f];
+            const double i2 = d == 0 ? p.ih2[0] : (d == 1 ? p.ih2[1] : p.ih2[2]);
+            const double f2 = (q & 1) ? i2 : -i2;
+#pragma unroll
+            for (int f = 0; f < ND; ++f) {
+              const double wo = d == 0 ? wx[f] : (d == 1 ? wy[f] : wz[f]);
+              x[f] += wo * f2 * slope(pp, des_code(f), p.komega);
+            }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int f = 0; f < ND; ++f) {
+      xp[f] = x[f];
+      zp[f] = wz[f];
+    }
+    fp = fc;
+    kb = kbn;
+    wb = wbn;
+    cc = cp;
+    cp = cn;
   }
-  xu[D] = x[0];
-  xv[D] = x[1];
-  xw[D] = x[2];
-  xk[D] = x[3];
-  xo[D] = x[4];
+  if (!d3 && inner) store(0);
 }
 
 void launch_destroy_adjoint(const Geom& g, const Phys& ph, const uint8_t* type,
                             const DevPatch* pt, const double* const st[5], double tau,
-                            const double* kb, const double* wb, double* E, double* M,
-                            double* const xb[5], hipStream_t s) {
-  const DesState S{st[0], st[1], st[2], st[3], st[4]};
-  const dim3 G = adj_grid(g), B(ABX, ABY);
-  hipLaunchKernelGGL(k_adj_des_weights, G, B, 0, s, g, ph, type, pt, S, tau, kb, wb, E, M);
-  hipLaunchKernelGGL(k_adj_des_gather, G, B, 0, s, g, ph, type, pt, S, tau, kb, wb, E, M, xb[0],
-                     xb[1], xb[2], xb[3], xb[4]);
+                            const double* kb, const double* wb, double* const xb[5],
+                            hipStream_t s) {
+  const AdjParams p = adj_params(g, ph, DS_RY);
+  DesIo io;
+  for (int f = 0; f < ND; ++f) {
+    io.s[f] = st[f];
+    io.x[f] = xb[f];
+  }
+  io.kb = kb;
+  io.wb = wb;
+  hipLaunchKernelGGL(k_adj_destroy, adj_grid(p), dim3(ABX, DS_RY), 0, s, p, type, pt, tau, io);
 }
 
 // ---- helpers of the whole step's reverse mode ------------------------------------

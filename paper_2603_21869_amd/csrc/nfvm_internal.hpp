@@ -162,25 +162,22 @@ constexpr uint32_t FACE_CODE_INACTIVE = 0xFFFFu;
 void launch_face_codes(const Geom& g, const uint8_t* cls, const float* cx, const float* cy,
                        const float* cz, uint16_t* code, hipStream_t s);
 
-// Reverse mode of the explicit stage (forward Euler) at the state st (seven
-// padded FP64 arrays u v w p theta k omega, theta = T - T_ref; p is not
-// read and may be null): from the
+// Reverse mode of the explicit stage (forward Euler) at the dense state st
+// (u v w T k omega, T absolute; the Jacobian does not depend on p): from the
 // dense adjoints yb of the outputs u v w T k omega, the dense adjoints xb of
-// the inputs u v w p T k omega, nu_t being the closure of k and omega.
-// W (6 padded arrays), pass (2), L4S (6) and nu (1, nu_t) are scratch.
+// the inputs u v w p T k omega, nu_t being the closure of k and omega.  No
+// output may alias an input.
 void launch_explicit_adjoint(const Geom& g, const Phys& ph, const uint8_t* type,
-                             const DevPatch* pt, const double* const st[7],
-                             const double* const yb[6], double* W, double* pass, double* L4S,
-                             double* nu, double* const xb[7], hipStream_t s);
+                             const DevPatch* pt, const double* const st[6],
+                             const double* const yb[6], double* const xb[7], hipStream_t s);
 
-// Reverse mode of the destruction step over tau at the state st (five
-// padded FP64 arrays u v w k omega): from the dense adjoints kb, wb of its k
-// and omega, the dense adjoints xb of u v w k omega.  E (6 padded arrays)
-// and M (9) are scratch.
+// Reverse mode of the destruction step over tau at the dense state st (u v w
+// k omega): from the dense adjoints kb, wb of its k and omega, the dense
+// adjoints xb of u v w k omega.  No output may alias an input.
 void launch_destroy_adjoint(const Geom& g, const Phys& ph, const uint8_t* type,
                             const DevPatch* pt, const double* const st[5], double tau,
-                            const double* kb, const double* wb, double* E, double* M,
-                            double* const xb[5], hipStream_t s);
+                            const double* kb, const double* wb, double* const xb[5],
+                            hipStream_t s);
 
 // out = scale (a + b) over n dense FP64 values; zeroing of a dense array on
 // the cells whose omega is held (wall-adjacent fluid cells).
