@@ -1057,10 +1057,10 @@ class GridT : public GridBase {
     return nf * (2 * sf + 1) + nc * (sc + 1);
   }
   // the bottom solver: its top level's b read and x written, the constant
-  // LDS image read; the coarsest dense solve: the inverse and its vectors
+  // constants and its matrix read; the coarsest dense solve: the inverse and its vectors
   double bottom_bytes_moved() const {
     const double nt = (double)lv[bottom_top].g.cells(), sc = elem_size(bottom_top);
-    return nt * 2 * sc + (double)(bot.lds_bytes - bot.zero_bytes);
+    return nt * 2 * sc + (double)bot_img_bytes;
   }
   double coarse_bytes_moved() const {
     const double n = (double)n_coarse, sc = elem_size(L - 1);
@@ -1088,9 +1088,9 @@ class GridT : public GridBase {
   FieldSet<V, F> rk2{};
   Bottom bot{};
 
-  // LDS layout of the bottom solver: iterates and right-hand sides of every
-  // level first (cleared per launch), then face coefficients, class bytes and
-  // the compact indices of the coarsest cells.
+  // Which levels the bottom solver takes: as many of the lowest ones as have
+  // at most one workgroup's LDS of cells (counted as iterates, right-hand side,
+  // face coefficients, damping and class bytes of every cell).
   static size_t al16(size_t v) { return (v + 15) & ~(size_t)15; }
   static size_t faces_bytes(const Geom& g) {
     size_t f = (size_t)(g.nx + 1) * g.ny * g.nz + (size_t)g.nx * (g.ny + 1) * g.nz;
@@ -1112,16 +1112,18 @@ class GridT : public GridBase {
     int top = L;
     for (int l = L - 1; l >= 1; --l) {
       const size_t need = bytes + bottom_bytes(lv[l].g);
-      if (need > limit || L - l > BOTTOM_MAX_LEVELS) break;
+      if (need > limit || L - l > BOTTOM_MAX_LEVELS || lv[l].g.cells() > 5 * BOTTOM_THREADS) break;
       bytes = need;
       top = l;
     }
     if (top > L - 2) return;  // fewer than two levels would fit
-    bottom_top = top;
+    bot = Bottom{};
     bot.nlev = L - top;
     bot.nu1 = pre_of(top);  // (every level of the bottom solver is a coarse one)
     bot.nu2 = post_of(top);
     bot.wj = wj;
+    bot.m = bot.nlev - 1;
+    while (bot.m > 0 && lv[top + bot.m - 1].g.cells() <= 64) --bot.m;
     size_t off = 0;
     for (int l = top; l < L; ++l) {
       BottomLevel& b = bot.lv[l - top];
@@ -1131,39 +1133,67 @@ class GridT : public GridBase {
       b.cf1 = lv[l].cf[1];
       b.cf2 = desc.dim == 3 ? lv[l].cf[2] : lv[l].cf[0];
       b.n = (int)lv[l].g.cells();
-      b.bx0 = (int)off;
-      b.bx1 = (int)(off + b.n * sizeof(C));
-      b.bb = (int)(off + 2 * b.n * sizeof(C));
-      off = al16(off + 3 * b.n * sizeof(C));
-    }
-    bot.zero_bytes = (int)off;
-    for (int l = top; l < L; ++l) {
-      BottomLevel& b = bot.lv[l - top];
-      const Geom& g = lv[l].g;
-      b.bfx = (int)off;
-      b.bfy = (int)(off + (size_t)(g.nx + 1) * g.ny * g.nz * sizeof(float));
-      b.bfz = (int)(b.bfy + (size_t)g.nx * (g.ny + 1) * g.nz * sizeof(float));
-      off += faces_bytes(g);
-      b.bwd = (int)off;
-      off += al16(g.cells() * sizeof(C));
-      b.bcl = (int)off;
+      const Geom& g = b.g;
+      b.ih2[0] = 1.0 / (g.hx * g.hx);
+      b.ih2[1] = 1.0 / (g.hy * g.hy);
+      b.ih2[2] = 1.0 / (g.hz * g.hz);
       b.inx = 1.0f / (float)g.nx;
       b.inxy = 1.0f / ((float)g.nx * (float)g.ny);
-      off += al16(g.cells());
+      b.bx0 = (int)off;
+      off = al16(off + (b.n + 1) * sizeof(C));
+      b.bx1 = (int)off;
+      off = al16(off + (b.n + 1) * sizeof(C));
+      b.bb = (int)off;
+      off = al16(off + b.n * sizeof(C));
+    }
+    bot.const_off = (int)off;
+    // (a top level of at most 64 cells is run by one wave from LDS too)
+    for (int l = bot.m > 0 ? top + 1 : top; l < L; ++l) {
+      BottomLevel& b = bot.lv[l - top];
+      b.bcf = (int)off;
+      off = al16(off + (size_t)6 * b.n * sizeof(float));
+      if (l == L - 1) continue;
+      b.bnb = (int)off;
+      off = al16(off + (size_t)4 * b.n * sizeof(uint32_t));
+      b.bwd = (int)off;
+      off = al16(off + b.n * sizeof(C));
     }
     bot.bcidx = (int)off;
-    off += al16(COARSE_MAX * sizeof(int));
+    off += al16(n_coarse * sizeof(int));
+    const size_t mat_bytes = al16((size_t)n_coarse * n_coarse * sizeof(C));
+    bot.mat_lds = lv[L - 1].g.cells() <= 64 && off + mat_bytes <= limit;
+    bot.bmat = (int)off;
+    if (bot.mat_lds) off += mat_bytes;
+    bot.const_bytes = (int)(off - bot.const_off);
+    bot.lds_bytes = off;
+    if (off > limit) {
+      // (not reached: the layout is smaller than the count above)
+      return;
+    }
+    bottom_top = top;
+    const int n0 = bot.lv[0].n;
+    bot.q = std::max(2, (n0 + BOTTOM_THREADS - 1) / BOTTOM_THREADS);
     bot.cmap = cmap;
     bot.ncount = ncount;
     bot.ainv = work;
+    bot.nco = n_coarse;
     bot.max_n = COARSE_MAX;
-    bot.lds_bytes = off;
-    if (off - bot.zero_bytes > bot_img_bytes) {
-      bot_img_bytes = off - bot.zero_bytes;
-      bot_img = alloc<unsigned char>(bot_img_bytes, "bottom LDS image");
+    const size_t t_nb = al16((size_t)4 * n0 * 4), t_cf = al16((size_t)6 * n0 * 4),
+                 t_wd = al16(n0 * sizeof(C)), t_img = al16(bot.const_bytes);
+    const size_t total = t_nb + t_cf + t_wd + t_img;
+    if (total > bot_img_bytes) {
+      bot_img_bytes = total;
+      bot_img = alloc<unsigned char>(bot_img_bytes, "bottom constants");
     }
-    bot.img = bot_img;
-    launch_bottom_image<C>(bot, bot_img, stream);
+    unsigned char* q = bot_img;
+    bot.top_nb = (const uint32_t*)q;
+    bot.top_cf = (const float*)(q += t_nb);
+    bot.top_wd = q += t_cf;
+    bot.img = q += t_wd;
+    // (the transposed inverse, when it is not in LDS: the half of its buffer
+    // that only the elimination uses)
+    bot.mat = work + (size_t)COARSE_MAX * COARSE_MAX;
+    launch_bottom_setup<C>(bot, stream);
     NFVM_CK(hipGetLastError());
   }
   unsigned char* bot_img = nullptr;

@@ -2242,80 +2242,37 @@ void launch_finalize(int nv, int op, const RedBuf& red, int nblocks, int slot0, 
 }
 
 // ---- LDS bottom solver ----------------------------------------------------------------
-// The same operators as the per-level kernels on compact LDS arrays (cell
-// index (k ny + j) nx + i).  Everything a phase reads lives in LDS: iterates,
-// right-hand side, class bytes and the face coefficients (x faces
-// (nx+1) ny nz, y faces nx (ny+1) nz, z faces nx ny (nz+1), low face of cell
-// c at its own index, high face one row/plane further).  Neighbours outside
-// the box read as 0 and inactive cells hold 0, as in global memory.
-// The workgroup's dynamic LDS.  Level arrays are addressed as byte offsets
-// from it (pointers kept in memory would lose the LDS address space and
-// turn every access into a flat one).
+// One workgroup runs the V-cycle of the lowest levels with every iterate and
+// right-hand side in LDS, on compact arrays (cell index (k ny + j) nx + i).
+// Its time is the length of its chain of phases, so:
+//   - a cell's constants (indices of its six neighbours and of its parent, six
+//     face coefficients, wj / D) are formed once per grid.  A thread keeps those
+//     of its cells of the top level (t, t + 1024, ...) and their iterates in
+//     registers through all its sweeps; the lower levels' sit in LDS.  A sweep
+//     then reads six values per cell and writes one.  The neighbour past the
+//     box is a slot that holds 0, and inactive cells have wj / D = 0, so no
+//     phase tests positions or classes.
+//   - levels of at most 64 cells are run by the first wave, one cell per lane
+//     with its constants in registers: LDS operations of one wave take effect
+//     in order, so its phases need no workgroup barrier.
+//   - the coarsest level's inverse is held transposed, so the threads of a wave,
+//     one row each, read consecutive values.
+// Every value is formed by the operations of the per-level kernels in their
+// order.  Bound by the vector instructions of one CU on the top level and by
+// latency below it; with 4096 top cells and 6 + 6 sweeps 3.7 us load the
+// constants, a sweep of the top level takes 0.8 us, a phase of the 512-cell
+// level 0.5.  Per launch, against constants read from LDS and positions and
+// classes tested in every phase: 64^3-channel grids (4096 cells, 2 + 2 sweeps,
+// eight in a batch) 34.3 -> 21.8 us, the 256 x 64 x 64 channel in FP64 (2048)
+// 23.5 -> 14.5, the 256 x 128 x 64 room (4096, 6 + 6) 57 -> 28, a room whose
+// coarsest level has 455 cells 84 -> 28.  Not used: the coarsest levels as one
+// dense matrix (changes the rounding of every cycle); for the larger dense
+// solve explicit batches of 16 or 32 columns (31 / 47 us) or reading the
+// inverse into the L2 in phase 0 (37 us).
+// The workgroup's dynamic LDS; arrays are addressed as byte offsets from it
+// (pointers kept in memory would lose the LDS address space and turn every
+// access into a flat one).
 extern __shared__ __align__(16) unsigned char bot_lds[];
-
-template <class C>
-struct LdsLevel {
-  int n, nx, ny, nz, d3;
-  float inx, inxy;
-  C ih2x, ih2y, ih2z;
-  int ox0, ox1, ob, ofx, ofy, ofz, owd, ocl;  // byte offsets in bot_lds
-  __device__ C* x0() const { return (C*)(bot_lds + ox0); }
-  __device__ C* x1() const { return (C*)(bot_lds + ox1); }
-  __device__ C* b() const { return (C*)(bot_lds + ob); }
-  __device__ const float* fx() const { return (const float*)(bot_lds + ofx); }
-  __device__ const float* fy() const { return (const float*)(bot_lds + ofy); }
-  __device__ const float* fz() const { return (const float*)(bot_lds + ofz); }
-  __device__ const C* wd() const { return (const C*)(bot_lds + owd); }
-  __device__ const uint8_t* cls() const { return bot_lds + ocl; }
-};
-
-template <class C>
-__device__ __forceinline__ LdsLevel<C> lds_level(const BottomLevel& L) {
-  LdsLevel<C> v;
-  v.n = L.n;
-  v.nx = L.g.nx;
-  v.ny = L.g.ny;
-  v.nz = L.g.nz;
-  v.d3 = L.g.dim == 3;
-  v.ih2x = (C)(1.0 / (L.g.hx * L.g.hx));
-  v.ih2y = (C)(1.0 / (L.g.hy * L.g.hy));
-  v.ih2z = (C)(1.0 / (L.g.hz * L.g.hz));
-  v.ox0 = L.bx0;
-  v.ox1 = L.bx1;
-  v.ob = L.bb;
-  v.ofx = L.bfx;
-  v.ofy = L.bfy;
-  v.ofz = L.bfz;
-  v.owd = L.bwd;
-  v.ocl = L.bcl;
-  v.inx = L.inx;
-  v.inxy = L.inxy;
-  return v;
-}
-
-// A x at compact cell c = (i, j, k).
-template <class C>
-__device__ __forceinline__ C lds_apply(const LdsLevel<C>& L, const C* x, int c, int i, int j,
-                                       int k, C xP) {
-  const int nxy = L.nx * L.ny;
-  const int fxl = (k * L.ny + j) * (L.nx + 1) + i;
-  const float* fx = L.fx();
-  const C cxl = (C)fx[fxl], cxh = (C)fx[fxl + 1];
-  const C xw = i > 0 ? x[c - 1] : (C)0, xe = i < L.nx - 1 ? x[c + 1] : (C)0;
-  C s = (cxl * (xP - xw) + cxh * (xP - xe)) * L.ih2x;
-  const int fyl = (k * (L.ny + 1) + j) * L.nx + i;
-  const float* fy = L.fy();
-  const C cyl = (C)fy[fyl], cyh = (C)fy[fyl + L.nx];
-  const C xs = j > 0 ? x[c - L.nx] : (C)0, xn = j < L.ny - 1 ? x[c + L.nx] : (C)0;
-  s += (cyl * (xP - xs) + cyh * (xP - xn)) * L.ih2y;
-  if (L.d3) {
-    const float* fz = L.fz();
-    const C czl = (C)fz[c], czh = (C)fz[c + nxy];
-    const C xb = k > 0 ? x[c - nxy] : (C)0, xt = k < L.nz - 1 ? x[c + nxy] : (C)0;
-    s += (czl * (xP - xb) + czh * (xP - xt)) * L.ih2z;
-  }
-  return s;
-}
 
 // q = n / d for 0 <= n < 2^22 from a float reciprocal of d, corrected to the
 // exact integer quotient.
@@ -2325,287 +2282,579 @@ __device__ __forceinline__ int qdiv(int n, int d, float inv) {
   q += (r >= d) - (r < 0);
   return q;
 }
-
-template <class C>
-__device__ __forceinline__ void lds_ijk(const LdsLevel<C>& L, int c, int& i, int& j, int& k) {
-  k = qdiv(c, L.nx * L.ny, L.inxy);
-  const int r = c - k * L.nx * L.ny;
-  j = qdiv(r, L.nx, L.inx);
-  i = r - j * L.nx;
+__device__ __forceinline__ void lds_ijk(const BottomLevel& L, int c, int& i, int& j, int& k) {
+  const int nxy = L.g.nx * L.g.ny;
+  k = qdiv(c, nxy, L.inxy);
+  const int r = c - k * nxy;
+  j = qdiv(r, L.g.nx, L.inx);
+  i = r - j * L.g.nx;
 }
 
-__device__ __forceinline__ void lds_cell(int nx, int ny, int c, int& i, int& j, int& k) {
-  i = c % nx;
-  j = (c / nx) % ny;
-  k = c / (nx * ny);
+// Parent word of a cell: its parent's compact index (bits 0-12), the sides it
+// lies on within the parent (13-15: x, y, z; 1 = high), whether the coarse
+// neighbours on those sides are inside the box (16-18), and which of the
+// coarse cells its interpolation reads are active: (parent, y, z, yz
+// neighbours) in bits 19-22 and their x neighbours in bits 23-26.  Positions
+// outside the box are clamped to the cell itself.
+constexpr int PW_SIDE = 13, PW_IN = 16, PW_ACT = 19, PW_NACT = 23;
+
+// The constants of cell c of level l: neighbour indices (two 16-bit LDS byte
+// offsets in an iterate per word, x-/x+, y-/y+, z-/z+; that of slot n past the box), face coefficients,
+// wj / D, and the parent word (not on the coarsest level).
+template <class C>
+__device__ void bottom_cell(const Bottom& B, int l, int c, uint32_t (&w)[4], float (&cf)[6],
+                            C& wd) {
+  const BottomLevel& L = B.lv[l];
+  const Geom& g = L.g;
+  const int nx = g.nx, ny = g.ny, nz = g.nz, nxy = nx * ny;
+  const int i = c % nx, j = (c / nx) % ny, k = c / nxy;
+  const int P = g.idx(i, j, k);
+  const bool act = L.cls[P] != MG_INACTIVE, d3 = g.dim == 3;
+  const int pos[3] = {i, j, k}, nn[3] = {nx, ny, nz}, st[3] = {1, nx, nxy};
+  const int ps[3] = {1, g.sx, g.sxy};
+  const float* cfa[3] = {L.cf0, L.cf1, L.cf2};
+  for (int d = 0; d < 3; ++d) {
+    const bool on = d < 2 || d3;
+    const uint32_t lo = on && pos[d] > 0 ? c - st[d] : L.n;
+    const uint32_t hi = on && pos[d] < nn[d] - 1 ? c + st[d] : L.n;
+    w[d] = (uint32_t)(lo * sizeof(C)) | ((uint32_t)(hi * sizeof(C)) << 16);
+    cf[2 * d] = act && on ? cfa[d][P] : 0.f;
+    cf[2 * d + 1] = act && on ? cfa[d][P + ps[d]] : 0.f;
+  }
+  // the diagonal in the level's arithmetic type, as the sweep kernels form it
+  C dg = ((C)cf[0] + (C)cf[1]) * (C)L.ih2[0] + ((C)cf[2] + (C)cf[3]) * (C)L.ih2[1];
+  if (d3) dg += ((C)cf[4] + (C)cf[5]) * (C)L.ih2[2];
+  wd = act ? (C)B.wj / dg : (C)0;
+  w[3] = 0;
+  if (l == B.nlev - 1) return;
+  const BottomLevel& K = B.lv[l + 1];
+  const int I = i >> 1, J = j >> 1, Kz = d3 ? k >> 1 : 0;
+  const int side[3] = {i & 1, j & 1, d3 ? k & 1 : 0};
+  const int cp[3] = {I, J, Kz}, cn[3] = {K.g.nx, K.g.ny, K.g.nz};
+  int q[3];  // the coarse neighbour on the cell's side, clamped
+  uint32_t v = (uint32_t)((Kz * cn[1] + J) * cn[0] + I);
+  for (int d = 0; d < 3; ++d) {
+    const int t = cp[d] + (side[d] ? 1 : -1);
+    const bool in = (d < 2 || d3) && t >= 0 && t < cn[d];
+    q[d] = in ? t : cp[d];
+    v |= (uint32_t)side[d] << (PW_SIDE + d);
+    v |= (uint32_t)in << (PW_IN + d);
+  }
+  for (int r = 0; r < 4; ++r) {
+    const int Jr = (r & 1) ? q[1] : J, Kr = (r & 2) ? q[2] : Kz;
+    const bool in = (!(r & 1) || ((v >> (PW_IN + 1)) & 1)) && (!(r & 2) || ((v >> (PW_IN + 2)) & 1));
+    v |= (uint32_t)(in && K.cls[K.g.idx(I, Jr, Kr)] != MG_INACTIVE) << (PW_ACT + r);
+    v |= (uint32_t)(K.cls[K.g.idx(q[0], Jr, Kr)] != MG_INACTIVE) << (PW_NACT + r);
+  }
+  w[3] = act ? v : 0xFFFFFFFFu;  // (inactive cells take no correction)
 }
 
-// Builds the constant part of the bottom solver's LDS image (everything
-// from byte zero_bytes on) in global memory, once per grid.
+// Everything constant: the top level's arrays, the LDS image of the levels
+// below it, and the coarsest inverse in the compute type, transposed.
 template <class C>
-__global__ __launch_bounds__(1024) void k_bottom_image(Bottom B, unsigned char* __restrict__ img) {
-  const int t = threadIdx.x, NT = blockDim.x;
-  unsigned char* base = img - B.zero_bytes;  // LDS byte offsets index img + (off - zero_bytes)
-  const int nl = B.nlev;
-  for (int l = 0; l < nl; ++l) {
-    const BottomLevel& G = B.lv[l];
-    const Geom& g = G.g;
-    const int nx = g.nx, ny = g.ny, nz = g.nz;
-    uint8_t* cls = base + G.bcl;
-    float* fx = (float*)(base + G.bfx);
-    float* fy = (float*)(base + G.bfy);
-    float* fz = (float*)(base + G.bfz);
-    C* wd = (C*)(base + G.bwd);
-    const double ih2x = 1.0 / (g.hx * g.hx), ih2y = 1.0 / (g.hy * g.hy),
-                 ih2z = 1.0 / (g.hz * g.hz);
-    for (int c = t; c < G.n; c += NT) {
-      int i, j, k;
-      lds_cell(nx, ny, c, i, j, k);
-      const int P = g.idx(i, j, k);
-      cls[c] = G.cls[P];
-      // the diagonal in the level's arithmetic type, as the sweep kernels form it
-      C d = ((C)G.cf0[P] + (C)G.cf0[P + 1]) * (C)ih2x + ((C)G.cf1[P] + (C)G.cf1[P + g.sx]) * (C)ih2y;
-      if (g.dim == 3) d += ((C)G.cf2[P] + (C)G.cf2[P + g.sxy]) * (C)ih2z;
-      wd[c] = G.cls[P] == MG_INACTIVE ? (C)0 : (C)B.wj / d;
-    }
-    const int nfx = (nx + 1) * ny * nz;
-    for (int e = t; e < nfx; e += NT) {
-      const int i = e % (nx + 1), j = (e / (nx + 1)) % ny, k = e / ((nx + 1) * ny);
-      fx[e] = G.cf0[g.idx(i, j, k)];
-    }
-    const int nfy = nx * (ny + 1) * nz;
-    for (int e = t; e < nfy; e += NT) {
-      const int i = e % nx, j = (e / nx) % (ny + 1), k = e / (nx * (ny + 1));
-      fy[e] = G.cf1[g.idx(i, j, k)];
-    }
-    if (g.dim == 3) {
-      const int nfz = nx * ny * (nz + 1);
-      for (int e = t; e < nfz; e += NT) {
-        const int i = e % nx, j = (e / nx) % ny, k = e / (nx * ny);
-        fz[e] = G.cf2[g.idx(i, j, k)];
-      }
+__global__ __launch_bounds__(256) void k_bottom_setup(Bottom B) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x, NT = gridDim.x * blockDim.x;
+  unsigned char* img = (unsigned char*)B.img - B.const_off;  // indexed by LDS byte offsets
+  for (int l = 0; l < B.nlev; ++l) {
+    const BottomLevel& L = B.lv[l];
+    const bool regs = l == 0 && B.m > 0;
+    uint32_t* nb = regs ? (uint32_t*)B.top_nb : (uint32_t*)(img + L.bnb);
+    float* cfo = regs ? (float*)B.top_cf : (float*)(img + L.bcf);
+    C* wdo = regs ? (C*)B.top_wd : (C*)(img + L.bwd);
+    for (int c = t; c < L.n; c += NT) {
+      uint32_t w[4];
+      float cf[6];
+      C wd;
+      bottom_cell<C>(B, l, c, w, cf, wd);
+      for (int q = 0; q < 6; ++q) cfo[q * L.n + c] = cf[q];
+      if (l == B.nlev - 1) continue;
+      for (int q = 0; q < 4; ++q) nb[q * L.n + c] = w[q];
+      wdo[c] = wd;
     }
   }
-  int* cidx = (int*)(base + B.bcidx);
-  const int nco = *B.ncount;
-  const BottomLevel& G = B.lv[nl - 1];
-  if (nco <= B.max_n)
-    for (int a = t; a < nco; a += NT) {
-      const int P = B.cmap[a] - G.g.off;
-      const int kk = P / G.g.sxy, jj = (P % G.g.sxy) / G.g.sx, ii = P % G.g.sx;
-      cidx[a] = (kk * G.g.ny + jj) * G.g.nx + ii;
-    }
+  const int n = B.nco;
+  if (n > B.max_n) return;
+  const BottomLevel& L = B.lv[B.nlev - 1];
+  int* cidx = (int*)(img + B.bcidx);
+  for (int a = t; a < n; a += NT) {
+    const int P = B.cmap[a] - L.g.off;
+    const int kk = P / L.g.sxy, jj = (P % L.g.sxy) / L.g.sx, ii = P % L.g.sx;
+    cidx[a] = (kk * L.g.ny + jj) * L.g.nx + ii;
+  }
+  C* mat = B.mat_lds ? (C*)(img + B.bmat) : (C*)B.mat;
+  for (int e = t; e < n * n; e += NT) mat[(e % n) * n + e / n] = (C)B.ainv[e];
 }
 
 template <class C>
-void launch_bottom_image(const Bottom& B, void* img, hipStream_t s) {
-  hipLaunchKernelGGL(k_bottom_image<C>, dim3(1), dim3(1024), 0, s, B, (unsigned char*)img);
+void launch_bottom_setup(const Bottom& B, hipStream_t s) {
+  hipLaunchKernelGGL(k_bottom_setup<C>, dim3(16), dim3(256), 0, s, B);
 }
-template void launch_bottom_image<double>(const Bottom&, void*, hipStream_t);
-template void launch_bottom_image<float>(const Bottom&, void*, hipStream_t);
+template void launch_bottom_setup<double>(const Bottom&, hipStream_t);
+template void launch_bottom_setup<float>(const Bottom&, hipStream_t);
 
-template <class SC, class C>
+// A x at a cell with value xP from its neighbour words and coefficients.
+template <class C>
+__device__ __forceinline__ C lds_apply(const C (&ih2)[3], bool d3, const C* x,
+                                       const uint32_t (&w)[3], const float (&cf)[6], C xP) {
+  auto lo = [&](int d) { return *(const C*)((const unsigned char*)x + (w[d] & 0xFFFFu)); };
+  auto hi = [&](int d) { return *(const C*)((const unsigned char*)x + (w[d] >> 16)); };
+  C s = ((C)cf[0] * (xP - lo(0)) + (C)cf[1] * (xP - hi(0))) * ih2[0];
+  s += ((C)cf[2] * (xP - lo(1)) + (C)cf[3] * (xP - hi(1))) * ih2[1];
+  if (d3) s += ((C)cf[4] * (xP - lo(2)) + (C)cf[5] * (xP - hi(2))) * ih2[2];
+  return s;
+}
+
+// The correction of a cell from its parent word pw: the prolongation rules
+// (plane_rules, then the z step) on the compact arrays of the coarse level
+// (values e, coefficients cf[6][n], strides 1, sy, sz).
+template <class C>
+__device__ __forceinline__ C lds_prolong(uint32_t pw, bool d3, const C* e, const float* cf, int n,
+                                         int sy, int sz) {
+  const C w3 = (C)0.75, w1 = (C)0.25;
+  const int Q = (int)(pw & 0x1FFFu);
+  auto bit = [&](int b) { return ((pw >> b) & 1u) != 0; };
+  const bool inx = bit(PW_IN), iny = bit(PW_IN + 1), inz = bit(PW_IN + 2);
+  const int ox = inx ? (bit(PW_SIDE) ? 1 : -1) : 0;
+  const int oy = iny ? (bit(PW_SIDE + 1) ? sy : -sy) : 0;
+  const int oz = inz ? (bit(PW_SIDE + 2) ? sz : -sz) : 0;
+  const int R[4] = {Q, Q + oy, Q + oz, Q + oy + oz};
+  // boundary ghosts (1 - c_f) on the sides that leave the box
+  C gx[4], gy[2], gz = 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) gx[r] = (C)0;
+  gy[0] = gy[1] = (C)0;
+  if (!inx) {
+    const float* f = cf + (bit(PW_SIDE) ? n : 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) gx[r] = (C)1 - (C)f[R[r]];
+  }
+  if (!iny) {
+    const float* f = cf + 2 * n + (bit(PW_SIDE + 1) ? n : 0);
+    gy[0] = (C)1 - (C)f[R[0]];
+    gy[1] = (C)1 - (C)f[R[2]];
+  }
+  if (d3 && !inz) gz = (C)1 - (C)cf[4 * n + (bit(PW_SIDE + 2) ? n : 0) + Q];
+  C X[4];
+  bool act[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    act[r] = bit(PW_ACT + r);
+    const C v = e[R[r]], nv = e[R[r] + ox];
+    const C nb = inx ? (bit(PW_NACT + r) ? nv : v) : gx[r] * v;
+    X[r] = act[r] ? w3 * v + w1 * nb : (C)0;
+  }
+  const C yn0 = iny ? (act[1] ? X[1] : X[0]) : gy[0] * X[0];
+  const C Y0 = act[0] ? w3 * X[0] + w1 * yn0 : (C)0;
+  if (!d3) return Y0;
+  const C yn1 = iny ? (act[3] ? X[3] : X[2]) : gy[1] * X[2];
+  const C Y1 = act[2] ? w3 * X[2] + w1 * yn1 : (C)0;
+  const C zn = inz ? (act[2] ? Y1 : Y0) : gz * Y0;
+  return w3 * Y0 + w1 * zn;
+}
+
+// What the phases of a level below the top read of it.
+template <class C>
+struct LdsLevel {
+  int n, nx, ny, nz, kz;
+  int ox0, ox1, ob, onb, ocf, owd;  // byte offsets in bot_lds
+  float inx, inxy;
+  C ih2[3];
+};
+
+// Residuals res of level F's cells averaged over the children of coarse cell
+// c (the pairs along x, then y, then z).
+template <class C>
+__device__ __forceinline__ C lds_children(const LdsLevel<C>& F, const LdsLevel<C>& K, bool d3,
+                                          const C* res, int c) {
+  const int kxy = K.nx * K.ny, fxy = F.nx * F.ny;
+  const int Kz = qdiv(c, kxy, K.inxy), r0 = c - Kz * kxy;
+  const int J = qdiv(r0, K.nx, K.inx), I = r0 - J * K.nx;
+  const C* r = res + (F.kz * Kz * F.ny + 2 * J) * F.nx + 2 * I;
+  C s = (r[0] + r[1]) + (r[F.nx] + r[F.nx + 1]);
+  if (d3) s += (r[fxy] + r[fxy + 1]) + (r[fxy + F.nx] + r[fxy + F.nx + 1]);
+  return s * (C)(d3 ? 0.125 : 0.25);
+}
+
+// Orders the LDS operations of one wave (which the hardware executes in
+// order) for the compiler.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The value of lane q (uniform over the wave).
+__device__ __forceinline__ float lane_value(float v, int q) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), q));
+}
+__device__ __forceinline__ double lane_value(double v, int q) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), q),
+                          __builtin_amdgcn_readlane(__double2loint(v), q));
+}
+
+// Row a of the n x n matrix (n <= 64) whose transpose is A, times b, of which
+// lane l holds element l: the terms are added one by one in column order, the
+// loads of 16 columns issued together (past the last one they repeat it).
+template <class C>
+__device__ __forceinline__ C row_times(const C* __restrict__ A, int n, int a, C b) {
+  C s = 0;
+  for (int q = 0; q < n; q += 16) {
+    C v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = A[min(q + u, n - 1) * n + a];
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (q + u < n) s += v[u] * lane_value(b, q + u);
+  }
+  return s;
+}
+
+// The V-cycle from level m down, run by one wave, one cell per lane (levels
+// of at most 64 cells; a larger coarsest level is solved by the whole
+// workgroup instead).  In: b of level m and, if it is swept, its first sweep
+// from zero in x0.  Returns which buffer holds level m's result.
+template <class C>
+__device__ __forceinline__ int bottom_wave(const Bottom& B, const LdsLevel<C>* lvs, bool d3,
+                                           int lane) {
+  const int m = B.m, nl = B.nlev, nu1 = B.nu1, nu2 = B.nu2;
+  const bool pre = nu1 > 0;
+  unsigned curm = 0;
+  auto buf = [&](const LdsLevel<C>& L, int l, bool other) {
+    return (C*)(bot_lds + ((((curm >> l) & 1u) != 0) != other ? L.ox1 : L.ox0));
+  };
+  // the lane's cell of level l
+  struct Cell {
+    uint32_t w[3], pw;
+    float f[6];
+    C wd, b;
+  };
+  auto cell = [&](const LdsLevel<C>& L, int c, Cell& q) {
+    const uint32_t* nbp = (const uint32_t*)(bot_lds + L.onb);
+    const float* cfp = (const float*)(bot_lds + L.ocf);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) q.w[d] = nbp[d * L.n + c];
+    q.pw = nbp[3 * L.n + c];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) q.f[d] = cfp[d * L.n + c];
+    q.wd = ((const C*)(bot_lds + L.owd))[c];
+    q.b = ((const C*)(bot_lds + L.ob))[c];
+  };
+  auto sweeps = [&](const LdsLevel<C>& L, int l, const Cell& q, int n) {
+    for (int s = 0; s < n; ++s) {
+      if (lane < L.n) {
+        const C* xin = buf(L, l, false);
+        const C xP = xin[lane];
+        buf(L, l, true)[lane] = xP + (q.b - lds_apply<C>(L.ih2, d3, xin, q.w, q.f, xP)) * q.wd;
+      }
+      curm ^= 1u << l;
+      wave_sync();
+    }
+  };
+  for (int l = m; l < nl - 1; ++l) {
+    const LdsLevel<C> L = lvs[l], K = lvs[l + 1];
+    Cell q;
+    if (lane < L.n) cell(L, lane, q);
+    sweeps(L, l, q, nu1 - 1);
+    C* res = buf(L, l, true);
+    if (lane < L.n) {
+      const C* xin = buf(L, l, false);
+      res[lane] = q.b - lds_apply<C>(L.ih2, d3, xin, q.w, q.f, xin[lane]);
+    }
+    wave_sync();
+    if (lane < K.n) {
+      const C bc = lds_children<C>(L, K, d3, res, lane);
+      ((C*)(bot_lds + K.ob))[lane] = bc;
+      if (l + 1 < nl - 1)
+        ((C*)(bot_lds + K.ox0))[lane] = pre ? bc * ((const C*)(bot_lds + K.owd))[lane] : (C)0;
+    }
+    wave_sync();
+  }
+  {  // the coarsest level: its dense inverse, one row per lane
+    const LdsLevel<C> L = lvs[nl - 1];
+    const int* cidx = (const int*)(bot_lds + B.bcidx);
+    const C* b = (const C*)(bot_lds + L.ob);
+    C* x = (C*)(bot_lds + L.ox0);
+    const int n = B.nco;
+    if (lane < L.n) x[lane] = (C)0;  // (inactive cells)
+    const int a = min(lane, max(n - 1, 0));
+    const C bl = lane < n ? b[cidx[lane]] : (C)0;
+    const C s = B.mat_lds ? row_times<C>((const C*)(bot_lds + B.bmat), n, a, bl)
+                          : row_times<C>((const C*)B.mat, n, a, bl);
+    if (lane < n) x[cidx[lane]] = s;
+    wave_sync();
+  }
+  for (int l = nl - 2; l >= m; --l) {
+    const LdsLevel<C> L = lvs[l], K = lvs[l + 1];
+    Cell q;
+    if (lane < L.n) {
+      cell(L, lane, q);
+      C* x = buf(L, l, false);
+      const C* e = buf(K, l + 1, false);
+      if (q.pw != 0xFFFFFFFFu)
+        x[lane] += lds_prolong<C>(q.pw, d3, e, (const float*)(bot_lds + K.ocf), K.n, K.nx,
+                                  K.nx * K.ny);
+    }
+    wave_sync();
+    sweeps(L, l, q, nu2);
+  }
+  return (int)((curm >> m) & 1u);
+}
+
+template <class SC, class C, int Q>
 __device__ __forceinline__ void bottom_body(const Bottom& B, const SC* __restrict__ btop,
                                             SC* __restrict__ xtop,
                                             const double* __restrict__ ctl) {
-  // the stopping flag is read with the image and tested after phase 0,
+  constexpr int NT = BOTTOM_THREADS;
+  // the stopping flag is read with the constants and tested after phase 0,
   // which writes only LDS
   const bool done = ctl[S_DONE] != 0.0;
-  const int t = threadIdx.x, NT = blockDim.x;
-  const int nl = B.nlev;
-  const bool pre = B.nu1 > 0;
+  const int t = threadIdx.x;
+  const int m = B.m, nl = B.nlev, nu1 = B.nu1, nu2 = B.nu2;
+  const bool pre = nu1 > 0;
+  const bool d3 = B.lv[0].g.dim == 3;
   // level descriptors, read from LDS by every phase (not from the kernel
   // arguments, whose scalar loads would stall each phase)
   __shared__ LdsLevel<C> lvs[BOTTOM_MAX_LEVELS];
-  if (t < nl) lvs[t] = lds_level<C>(B.lv[t]);
-  // ---- phase 0: constant image, cleared iterates, the top level's
-  // right-hand side and its first sweep from zero (disjoint LDS ranges)
-  {
-    const uint4* __restrict__ src = (const uint4*)B.img;
-    uint4* dst = (uint4*)(bot_lds + B.zero_bytes);
-    const int n16 = (int)((B.lds_bytes - (size_t)B.zero_bytes) / 16);
-    for (int e0 = t; e0 < n16; e0 += 4 * NT) {
-      // indices past the end re-read the last element (kept in registers)
-      const uint4 v0 = src[e0], v1 = src[min(e0 + NT, n16 - 1)];
-      const uint4 v2 = src[min(e0 + 2 * NT, n16 - 1)], v3 = src[min(e0 + 3 * NT, n16 - 1)];
-      dst[e0] = v0;
-      if (e0 + NT < n16) dst[e0 + NT] = v1;
-      if (e0 + 2 * NT < n16) dst[e0 + 2 * NT] = v2;
-      if (e0 + 3 * NT < n16) dst[e0 + 3 * NT] = v3;
-    }
-    const BottomLevel& G = B.lv[0];
-    // top level: x0 [bx0, bx1), x1 [bx1, bb), b [bb, ...): clear x1 and
-    // every later level's iterates and right-hand side
-    for (int e = G.bx1 / 4 + t; e < G.bb / 4; e += NT) ((float*)bot_lds)[e] = 0.f;
-    const int z1 = (int)((G.bb + (size_t)G.n * sizeof(C) + 15) & ~(size_t)15);
-    for (int e = z1 / 4 + t; e < B.zero_bytes / 4; e += NT) ((float*)bot_lds)[e] = 0.f;
-    // class bytes and wj / D of the top level straight from the image in
-    // global memory (the LDS copy is not complete before the barrier)
-    const uint8_t* gcl = (const uint8_t*)B.img + (G.bcl - B.zero_bytes);
-    const C* gwd = (const C*)((const uint8_t*)B.img + (G.bwd - B.zero_bytes));
-    C* x0 = (C*)(bot_lds + G.bx0);
-    C* bt = (C*)(bot_lds + G.bb);
-    const LdsLevel<C> L = lds_level<C>(G);
-    for (int c = t; c < G.n; c += NT) {
-      int i, j, k;
-      lds_ijk(L, c, i, j, k);
-      const C v = St<SC, C>::ld(btop + G.g.idx(i, j, k));
-      const bool act = gcl[c] != MG_INACTIVE;
-      bt[c] = v;
-      x0[c] = (pre && act) ? v * gwd[c] : (C)0;
+  __shared__ int wave_buf;
+  if (t < nl) {
+    const BottomLevel& L = B.lv[t];
+    LdsLevel<C> v;
+    v.n = L.n;
+    v.nx = L.g.nx;
+    v.ny = L.g.ny;
+    v.nz = L.g.nz;
+    v.kz = L.g.dim == 3 ? 2 : 1;
+    v.ox0 = L.bx0;
+    v.ox1 = L.bx1;
+    v.ob = L.bb;
+    v.onb = L.bnb;
+    v.ocf = L.bcf;
+    v.owd = L.bwd;
+    v.inx = L.inx;
+    v.inxy = L.inxy;
+    for (int d = 0; d < 3; ++d) v.ih2[d] = (C)L.ih2[d];
+    lvs[t] = v;
+    // the slots past the box
+    ((C*)(bot_lds + L.bx0))[L.n] = (C)0;
+    ((C*)(bot_lds + L.bx1))[L.n] = (C)0;
+  }
+  const int n0 = B.lv[0].n;
+  C* const X0 = (C*)(bot_lds + B.lv[0].bx0);
+  C* const X1 = (C*)(bot_lds + B.lv[0].bx1);
+  C* const BB = (C*)(bot_lds + B.lv[0].bb);
+  // ---- phase 0: this thread's cells of the top level, the lower levels'
+  // constants, the first sweep from zero (disjoint LDS ranges)
+  uint32_t nb[Q][3], pw[Q];
+  float cf[Q][6];
+  C wd[Q], bv[Q], xv[Q];
+  constexpr bool BREG = Q <= 2;  // (else the right-hand sides stay in LDS)
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int c = t + q * NT;
+    if (c >= n0) continue;
+    int i, j, k;
+    lds_ijk(B.lv[0], c, i, j, k);
+    bv[q] = St<SC, C>::ld(btop + B.lv[0].g.idx(i, j, k));
+    if (m > 0) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) nb[q][d] = B.top_nb[d * n0 + c];
+      pw[q] = B.top_nb[3 * n0 + c];
+#pragma unroll
+      for (int d = 0; d < 6; ++d) cf[q][d] = B.top_cf[d * n0 + c];
+      wd[q] = ((const C*)B.top_wd)[c];
     }
   }
-  int* cidx = (int*)(bot_lds + B.bcidx);
-  const int nco = *B.ncount;
+  {
+    const uint4* __restrict__ src = (const uint4*)B.img;
+    uint4* dst = (uint4*)(bot_lds + B.const_off);
+    const int n16 = B.const_bytes / 16;
+    for (int e = t; e < n16; e += NT) dst[e] = src[e];
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int c = t + q * NT;
+    if (c >= n0) continue;
+    if (m > 0) {
+      xv[q] = pre ? bv[q] * wd[q] : (C)0;
+      X0[c] = xv[q];
+    }
+    if (!BREG || m == 0) BB[c] = bv[q];
+  }
   __syncthreads();
   if (done) return;  // uniform over the workgroup
-  // current iterate buffer of every level, one bit per level (a bit mask
-  // rather than an array keeps it in a register); x0 holds the first sweep
-  unsigned curm = 0;
-  auto cur_of = [&](int l) -> int { return (int)((curm >> l) & 1u); };
-  // one damped-Jacobi sweep on level l (to global memory: the last sweep of
-  // the top level)
-  auto sweep = [&](int l, bool to_global) {
-    const LdsLevel<C> L = lvs[l];
-    const C* xin = cur_of(l) ? L.x1() : L.x0();
-    C* xout = cur_of(l) ? L.x0() : L.x1();
-    const uint8_t* cls = L.cls();
-    const C* bb = L.b();
-    const C* wd = L.wd();
-    for (int c = t; c < L.n; c += NT) {
-      if (cls[c] == MG_INACTIVE) continue;
+  const C ih2[3] = {(C)B.lv[0].ih2[0], (C)B.lv[0].ih2[1], (C)B.lv[0].ih2[2]};
+  if (m == 0) {  // a top level of at most 64 cells
+    if (t >= 64) return;
+    const LdsLevel<C> L = lvs[0];
+    if (t < L.n) X0[t] = pre ? BB[t] * ((const C*)(bot_lds + L.owd))[t] : (C)0;
+    wave_sync();
+    const C* x = bottom_wave<C>(B, lvs, d3, t) ? X1 : X0;
+    if (t < L.n) {
       int i, j, k;
-      lds_ijk(L, c, i, j, k);
-      const C xP = xin[c];
-      const C v = xP + (bb[c] - lds_apply<C>(L, xin, c, i, j, k, xP)) * wd[c];
-      if (to_global)
+      lds_ijk(B.lv[0], t, i, j, k);
+      St<SC, C>::st(xtop + B.lv[0].g.idx(i, j, k), x[t]);
+    }
+    return;
+  }
+  int cur = 0;        // the top level's current iterate buffer
+  unsigned curm = 0;  // the lower levels', one bit per level
+  // one damped-Jacobi sweep on the top level (to global memory: the last one)
+  auto sweep0 = [&](bool to_global) {
+    const C* xin = cur ? X1 : X0;
+    C* xout = cur ? X0 : X1;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int c = t + q * NT;
+      if (c >= n0) continue;
+      const C b = BREG ? bv[q] : BB[c];
+      const C v = xv[q] + (b - lds_apply<C>(ih2, d3, xin, nb[q], cf[q], xv[q])) * wd[q];
+      if (to_global) {
+        int i, j, k;
+        lds_ijk(B.lv[0], c, i, j, k);
         St<SC, C>::st(xtop + B.lv[0].g.idx(i, j, k), v);
-      else
+      } else {
         xout[c] = v;
+      }
+      xv[q] = v;
+    }
+    cur ^= 1;
+    if (!to_global) __syncthreads();
+  };
+  // a cell of a lower level, from LDS
+  auto low_cell = [&](const LdsLevel<C>& L, int c, uint32_t (&w)[3], float (&f)[6]) {
+    const uint32_t* nbp = (const uint32_t*)(bot_lds + L.onb);
+    const float* cfp = (const float*)(bot_lds + L.ocf);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) w[d] = nbp[d * L.n + c];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) f[d] = cfp[d * L.n + c];
+  };
+  auto sweep = [&](int l) {
+    const LdsLevel<C> L = lvs[l];
+    const bool c1 = (curm >> l) & 1u;
+    const C* xin = (const C*)(bot_lds + (c1 ? L.ox1 : L.ox0));
+    C* xout = (C*)(bot_lds + (c1 ? L.ox0 : L.ox1));
+    const C* bb = (const C*)(bot_lds + L.ob);
+    const C* wdp = (const C*)(bot_lds + L.owd);
+    for (int c = t; c < L.n; c += NT) {
+      uint32_t w[3];
+      float f[6];
+      low_cell(L, c, w, f);
+      const C xP = xin[c];
+      xout[c] = xP + (bb[c] - lds_apply<C>(L.ih2, d3, xin, w, f, xP)) * wdp[c];
     }
     curm ^= 1u << l;
     __syncthreads();
   };
-  // ---- down the hierarchy
-  for (int l = 0; l < nl - 1; ++l) {
-    for (int s = 1; s < B.nu1; ++s) sweep(l, false);
-    // residual and restriction in one phase: 8 consecutive lanes take the 8
-    // children of one coarse cell and sum their residuals by lane exchange;
-    // the coarse level's first sweep from zero follows at once
-    const LdsLevel<C> F = lvs[l];
-    const LdsLevel<C> Cc = lvs[l + 1];
-    const C* x = cur_of(l) ? F.x1() : F.x0();
-    const uint8_t* fcls = F.cls();
-    const uint8_t* ccls = Cc.cls();
-    const int kz = Cc.d3 ? 2 : 1;
-    const int ncl8 = Cc.n * 8;
-    for (int base = 0; base < ncl8; base += NT) {  // uniform trip count
-      const int q = base + t;
-      const int c = q >> 3, ch = q & 7;
-      C r = 0;
-      const bool cact = q < ncl8 && ccls[c] != MG_INACTIVE;
-      int I = 0, J = 0, K = 0;
-      if (cact) lds_ijk(Cc, c, I, J, K);
-      const int a = ch & 1, bj = (ch >> 1) & 1, cc = ch >> 2;
-      if (cact && cc < kz) {
-        const int i = 2 * I + a, j = 2 * J + bj, k = kz * K + cc;
-        const int fc = (k * F.ny + j) * F.nx + i;
-        if (fcls[fc] != MG_INACTIVE) r = F.b()[fc] - lds_apply<C>(F, x, fc, i, j, k, x[fc]);
-      }
-      r += __shfl_xor(r, 1);
-      r += __shfl_xor(r, 2);
-      r += __shfl_xor(r, 4);
-      if (cact && ch == 0) {
-        const C bc = r * (C)(kz == 2 ? 0.125 : 0.25);
-        Cc.b()[c] = bc;
-        Cc.x0()[c] = pre ? bc * Cc.wd()[c] : (C)0;
-      }
+  // level l's residuals (res) into level l + 1's right-hand side, with its
+  // first sweep from zero
+  auto restrict_from = [&](const LdsLevel<C>& F, const C* res, int l) {
+    const LdsLevel<C> K = lvs[l + 1];
+    C* kb = (C*)(bot_lds + K.ob);
+    C* kx = (C*)(bot_lds + K.ox0);
+    const C* kwd = (const C*)(bot_lds + K.owd);
+    for (int c = t; c < K.n; c += NT) {
+      const C bc = lds_children<C>(F, K, d3, res, c);
+      kb[c] = bc;
+      if (l + 1 < nl - 1) kx[c] = pre ? bc * kwd[c] : (C)0;
     }
     __syncthreads();
-  }
-  // ---- coarsest level: dense inverse
+  };
+  // ---- down the hierarchy
+  for (int s = 1; s < nu1; ++s) sweep0(false);
   {
-    const LdsLevel<C> L = lvs[nl - 1];
-    curm &= ~(1u << (nl - 1));
-    if (nco <= B.max_n) {
-      for (int a = t; a < nco; a += NT) {
-        C s = 0;
-        const double* row = B.ainv + (size_t)a * nco;
-        for (int q = 0; q < nco; ++q) s += (C)row[q] * L.b()[cidx[q]];
-        L.x0()[cidx[a]] = s;
-      }
+    const C* xin = cur ? X1 : X0;
+    C* res = cur ? X0 : X1;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int c = t + q * NT;
+      if (c < n0)
+        res[c] = (BREG ? bv[q] : BB[c]) - lds_apply<C>(ih2, d3, xin, nb[q], cf[q], xv[q]);
     }
+    __syncthreads();
+    restrict_from(lvs[0], res, 0);
+  }
+  for (int l = 1; l < m; ++l) {
+    for (int s = 1; s < nu1; ++s) sweep(l);
+    const LdsLevel<C> L = lvs[l];
+    const bool c1 = (curm >> l) & 1u;
+    const C* xin = (const C*)(bot_lds + (c1 ? L.ox1 : L.ox0));
+    C* res = (C*)(bot_lds + (c1 ? L.ox0 : L.ox1));
+    const C* bb = (const C*)(bot_lds + L.ob);
+    for (int c = t; c < L.n; c += NT) {
+      uint32_t w[3];
+      float f[6];
+      low_cell(L, c, w, f);
+      res[c] = bb[c] - lds_apply<C>(L.ih2, d3, xin, w, f, xin[c]);
+    }
+    __syncthreads();
+    restrict_from(L, res, l);
+  }
+  // ---- the levels of one wave, or a larger coarsest level: the rows of its
+  // inverse over the threads
+  if (lvs[m].n <= 64) {
+    if (t < 64) {
+      const int b = bottom_wave<C>(B, lvs, d3, t);
+      if (t == 0) wave_buf = b;
+    }
+    __syncthreads();
+    curm |= (unsigned)wave_buf << m;
+  } else {
+    const LdsLevel<C> L = lvs[m];
+    const int* cidx = (const int*)(bot_lds + B.bcidx);
+    const C* b = (const C*)(bot_lds + L.ob);
+    C* x = (C*)(bot_lds + L.ox0);
+    C* bc = (C*)(bot_lds + L.ox1);  // the active cells' right-hand sides, compact
+    const int n = B.nco;
+    const C* __restrict__ A = (const C*)B.mat;
+    for (int c = t; c < L.n; c += NT) x[c] = (C)0;  // (inactive cells)
+    for (int a = t; a < n; a += NT) bc[a] = b[cidx[a]];
+    __syncthreads();
+    if (n <= B.max_n)
+      for (int a = t; a < n; a += NT) {
+        C s = 0;
+#pragma unroll 16
+        for (int q = 0; q < n; ++q) s += A[(size_t)q * n + a] * bc[q];
+        x[cidx[a]] = s;
+      }
     __syncthreads();
   }
   // ---- up the hierarchy: prolongation and post-smoothing
-  for (int l = nl - 2; l >= 0; --l) {
-    const LdsLevel<C> F = lvs[l];
-    const LdsLevel<C> Cc = lvs[l + 1];
-    C* x = cur_of(l) ? F.x1() : F.x0();
-    const C* e = cur_of(l + 1) ? Cc.x1() : Cc.x0();
-    const bool d3 = Cc.d3;
-    const int cnx = Cc.nx, cny = Cc.ny, cnz = Cc.nz;
-    const uint8_t* ccls = Cc.cls();
-    const float* cfxa = Cc.fx();
-    const float* cfya = Cc.fy();
-    const float* cfza = Cc.fz();
-    auto cc_of = [&](int I, int J, int K) { return (K * cny + J) * cnx + I; };
-    const int nf = F.n;
-    const uint8_t* fcls = F.cls();
-    const bool direct = l == 0 && B.nu2 == 0;  // no post-sweep: write out here
-    for (int c = t; c < nf; c += NT) {
-      if (fcls[c] == MG_INACTIVE) continue;
-      int i, j, k;
-      lds_ijk(F, c, i, j, k);
-      // the prolongation rules (plane_rules, then the z step) on the compact
-      // arrays: indices outside the box are clamped to the cell itself and
-      // their values masked
-      const int I = i >> 1, J = j >> 1, K = d3 ? (k >> 1) : 0;
-      const int sx = (i & 1) ? 1 : -1, sy = (j & 1) ? 1 : -1, sz = (k & 1) ? 1 : -1;
-      const C w3 = (C)0.75, w1 = (C)0.25;
-      const bool inx = (unsigned)(I + sx) < (unsigned)cnx;
-      const bool iny = (unsigned)(J + sy) < (unsigned)cny;
-      const bool inz = d3 && (unsigned)(K + sz) < (unsigned)cnz;
-      const int In = inx ? I + sx : I, Jn = iny ? J + sy : J, Kn = inz ? K + sz : K;
-      const int Jq[4] = {J, Jn, J, Jn}, Kq[4] = {K, K, Kn, Kn};
-      C ev[4], en[4], cfx[4];
-      bool ac[4], an[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int Q = cc_of(I, Jq[q], Kq[q]), Qn = cc_of(In, Jq[q], Kq[q]);
-        ev[q] = e[Q];
-        en[q] = e[Qn];
-        ac[q] = ccls[Q] != MG_INACTIVE;
-        an[q] = ccls[Qn] != MG_INACTIVE;
-        cfx[q] = (C)cfxa[(Kq[q] * cny + Jq[q]) * (cnx + 1) + I + (sx > 0 ? 1 : 0)];
-      }
-      const C cfy0 = (C)cfya[(K * (cny + 1) + J + (sy > 0 ? 1 : 0)) * cnx + I];
-      const C cfy1 = (C)cfya[(Kn * (cny + 1) + J + (sy > 0 ? 1 : 0)) * cnx + I];
-      const C cfz = d3 ? (C)cfza[((K + (sz > 0 ? 1 : 0)) * cny + J) * cnx + I] : (C)0;
-      const bool act[4] = {ac[0], iny && ac[1], inz && ac[2], iny && inz && ac[3]};
-      C X[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const C nb = inx ? (an[q] ? en[q] : ev[q]) : ((C)1 - cfx[q]) * ev[q];
-        X[q] = act[q] ? w3 * ev[q] + w1 * nb : (C)0;
-      }
-      const C yn0 = iny ? (act[1] ? X[1] : X[0]) : ((C)1 - cfy0) * X[0];
-      const C Y0 = act[0] ? w3 * X[0] + w1 * yn0 : (C)0;
-      C Z = Y0;
-      if (d3) {
-        const C yn1 = iny ? (act[3] ? X[3] : X[2]) : ((C)1 - cfy1) * X[2];
-        const C Y1 = act[2] ? w3 * X[2] + w1 * yn1 : (C)0;
-        const C zn = inz ? (act[2] ? Y1 : Y0) : ((C)1 - cfz) * Y0;
-        Z = w3 * Y0 + w1 * zn;
-      }
-      const C v = x[c] + Z;
-      if (direct)
-        St<SC, C>::st(xtop + B.lv[0].g.idx(i, j, k), v);
-      else
-        x[c] = v;
+  for (int l = m - 1; l >= 1; --l) {
+    const LdsLevel<C> L = lvs[l], K = lvs[l + 1];
+    C* x = (C*)(bot_lds + (((curm >> l) & 1u) ? L.ox1 : L.ox0));
+    const C* e = (const C*)(bot_lds + (((curm >> (l + 1)) & 1u) ? K.ox1 : K.ox0));
+    const float* kcf = (const float*)(bot_lds + K.ocf);
+    const uint32_t* pwp = (const uint32_t*)(bot_lds + L.onb) + 3 * L.n;
+    for (int c = t; c < L.n; c += NT) {
+      const uint32_t w = pwp[c];
+      if (w != 0xFFFFFFFFu) x[c] += lds_prolong<C>(w, d3, e, kcf, K.n, K.nx, K.nx * K.ny);
     }
     __syncthreads();
-    for (int s = 0; s < B.nu2; ++s) sweep(l, l == 0 && s == B.nu2 - 1);
+    for (int s = 0; s < nu2; ++s) sweep(l);
+  }
+  {
+    const LdsLevel<C> K = lvs[1];
+    C* x = cur ? X1 : X0;
+    const C* e = (const C*)(bot_lds + (((curm >> 1) & 1u) ? K.ox1 : K.ox0));
+    const float* kcf = (const float*)(bot_lds + K.ocf);
+    const bool direct = nu2 == 0;  // no post-sweep: write out here
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int c = t + q * NT;
+      if (c >= n0) continue;
+      if (pw[q] != 0xFFFFFFFFu)
+        xv[q] += lds_prolong<C>(pw[q], d3, e, kcf, K.n, K.nx, K.nx * K.ny);
+      if (direct) {
+        int i, j, k;
+        lds_ijk(B.lv[0], c, i, j, k);
+        St<SC, C>::st(xtop + B.lv[0].g.idx(i, j, k), xv[q]);
+      } else {
+        x[c] = xv[q];
+      }
+    }
+    if (direct) return;
+    __syncthreads();
+    for (int s = 0; s < nu2; ++s) sweep0(s == nu2 - 1);
   }
 }
 
@@ -2618,29 +2867,43 @@ struct BottomArgsBase {
   const double* ctl;
 };
 
-template <class SC, class C>
-__global__ __launch_bounds__(1024) void k_bottom(Bottom B, const SC* __restrict__ btop,
-                                                 SC* __restrict__ xtop,
-                                                 const double* __restrict__ ctl) {
-  bottom_body<SC, C>(B, btop, xtop, ctl);
+template <class SC, class C, int Q>
+__global__ __launch_bounds__(BOTTOM_THREADS) void k_bottom(Bottom B, const SC* __restrict__ btop,
+                                                           SC* __restrict__ xtop,
+                                                           const double* __restrict__ ctl) {
+  bottom_body<SC, C, Q>(B, btop, xtop, ctl);
 }
 
-template <class SC, class C>
-__global__ __launch_bounds__(1024) void k_bottom_batch(const BottomArgsBase* __restrict__ a) {
+template <class SC, class C, int Q>
+__global__ __launch_bounds__(BOTTOM_THREADS) void k_bottom_batch(
+    const BottomArgsBase* __restrict__ a) {
   const BottomArgsBase& e = a[blockIdx.x];
-  bottom_body<SC, C>(e.B, (const SC*)e.btop, (SC*)e.xtop, e.ctl);
+  bottom_body<SC, C, Q>(e.B, (const SC*)e.btop, (SC*)e.xtop, e.ctl);
+}
+
+// Calls f with the kernel's slot count (Bottom::q) as a constant.
+template <class F>
+void bottom_slots(int q, F&& f) {
+  if (q <= 2)
+    f(std::integral_constant<int, 2>());
+  else if (q <= 3)
+    f(std::integral_constant<int, 3>());
+  else if (q <= 4)
+    f(std::integral_constant<int, 4>());
+  else
+    f(std::integral_constant<int, 5>());
 }
 
 // Dynamic LDS bytes one bottom workgroup may use on the current device: the
 // device's LDS per workgroup less the kernel's static LDS (its level table);
 // dynamic LDS above 64 KiB is enabled per kernel where the device has it.
-template <class SC, class C>
-size_t bottom_lds_limit() {
+template <class SC, class C, int Q>
+static size_t bottom_lds_limit_q() {
   int dev = 0, lim = 0;
   hipFuncAttributes fa;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&lim, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
-      hipFuncGetAttributes(&fa, (const void*)k_bottom<SC, C>) != hipSuccess) {
+      hipFuncGetAttributes(&fa, (const void*)k_bottom<SC, C, Q>) != hipSuccess) {
     (void)hipGetLastError();
     return 0;
   }
@@ -2648,14 +2911,20 @@ size_t bottom_lds_limit() {
   const int dyn = lim - stat;
   if (dyn <= 0) return 0;
   if (lim > 64 * 1024 &&
-      (hipFuncSetAttribute((const void*)k_bottom<SC, C>,
+      (hipFuncSetAttribute((const void*)k_bottom<SC, C, Q>,
                            hipFuncAttributeMaxDynamicSharedMemorySize, dyn) != hipSuccess ||
-       hipFuncSetAttribute((const void*)k_bottom_batch<SC, C>,
+       hipFuncSetAttribute((const void*)k_bottom_batch<SC, C, Q>,
                            hipFuncAttributeMaxDynamicSharedMemorySize, dyn) != hipSuccess)) {
     (void)hipGetLastError();
     return (size_t)(64 * 1024 - stat);
   }
   return (size_t)dyn;
+}
+template <class SC, class C>
+size_t bottom_lds_limit() {
+  return std::min(bottom_lds_limit_q<SC, C, 2>(),
+                  std::min(bottom_lds_limit_q<SC, C, 3>(),
+                           std::min(bottom_lds_limit_q<SC, C, 4>(), bottom_lds_limit_q<SC, C, 5>())));
 }
 template size_t bottom_lds_limit<double, double>();
 template size_t bottom_lds_limit<float, float>();
@@ -2664,8 +2933,10 @@ template size_t bottom_lds_limit<bf16, float>();
 template <class SC, class C>
 void launch_bottom(const Bottom& B, const void* btop, void* xtop, const double* ctl,
                    hipStream_t s) {
-  NFVM_LAUNCH((k_bottom<SC, C>), dim3(1), dim3(1024), B.lds_bytes, s, B, (const SC*)btop,
-                     (SC*)xtop, ctl);
+  bottom_slots(B.q, [&](auto q) {
+    NFVM_LAUNCH((k_bottom<SC, C, decltype(q)::value>), dim3(1), dim3(BOTTOM_THREADS), B.lds_bytes,
+                s, B, (const SC*)btop, (SC*)xtop, ctl);
+  });
 }
 template void launch_bottom<double, double>(const Bottom&, const void*, void*, const double*,
                                             hipStream_t);
@@ -2815,15 +3086,21 @@ bool wide_of(const MgGridDesc& d, int l) { return l == 0 || d.lv[l].wide; }
 // T: the single kernel for one grid, else one workgroup per grid.
 template <class T, class C>
 void emit_bottoms(BatchOps& o, const std::vector<BottomArgsBase>& bo, size_t lds) {
-  if (bo.size() == 1) {
-    const BottomArgsBase e = bo[0];
-    o.ops.push_back([=](const unsigned char*, hipStream_t s) {
-      hipLaunchKernelGGL((k_bottom<T, C>), dim3(1), dim3(1024), e.B.lds_bytes, s, e.B,
-                         (const T*)e.btop, (T*)e.xtop, e.ctl);
-    });
-  } else {
-    emit_blocks(o, bo, k_bottom_batch<T, C>, 1024, lds);
-  }
+  if (bo.empty()) return;
+  int q = 0;
+  for (const BottomArgsBase& e : bo) q = std::max(q, e.B.q);
+  bottom_slots(q, [&](auto qc) {
+    constexpr int Q = decltype(qc)::value;
+    if (bo.size() == 1) {
+      const BottomArgsBase e = bo[0];
+      o.ops.push_back([=](const unsigned char*, hipStream_t s) {
+        hipLaunchKernelGGL((k_bottom<T, C, Q>), dim3(1), dim3(BOTTOM_THREADS), e.B.lds_bytes, s,
+                           e.B, (const T*)e.btop, (T*)e.xtop, e.ctl);
+      });
+    } else {
+      emit_blocks(o, bo, k_bottom_batch<T, C, Q>, BOTTOM_THREADS, lds);
+    }
+  });
 }
 
 // Restrictions from a level of type A to one of type B, by kernel.

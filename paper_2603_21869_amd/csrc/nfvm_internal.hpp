@@ -344,8 +344,10 @@ void launch_mark_full(const Level& l, hipStream_t s);
 
 // One-workgroup V-cycle over levels top .. L-1 with the iterates and
 // right-hand sides held in LDS (compute precision); reads b of level top,
-// writes x[0] of level top.
+// writes x[0] of level top.  Levels top .. top + m - 1 are swept by the whole
+// workgroup, those of at most 64 cells below them by its first wave.
 constexpr int BOTTOM_MAX_LEVELS = 12;
+constexpr int BOTTOM_THREADS = 1024;
 struct BottomLevel {
   Geom g;
   const uint8_t* cls;
@@ -353,27 +355,44 @@ struct BottomLevel {
   const float* cf1;
   const float* cf2;
   int n;  // cells (nx * ny * nz)
-  // LDS byte offsets: iterates, right-hand side, x / y / z face
-  // coefficients, damping over diagonal (wj / D), class bytes
-  int bx0, bx1, bb, bfx, bfy, bfz, bwd, bcl;
+  // LDS byte offsets: iterates (n + 1 values each, the last one 0: the
+  // neighbour past the box) and right-hand side; below the top level also
+  // the cells' constants (face coefficients; on swept levels neighbour indices
+  // and parent word, and damping over diagonal wj / D)
+  int bx0, bx1, bb, bnb, bcf, bwd;
+  double ih2[3];    // 1 / h^2
   float inx, inxy;  // 1 / nx and 1 / (nx ny) for division-free cell indices
 };
 struct Bottom {
   int nlev;  // levels top .. L-1
+  int m;     // first level run by one wave (nlev - 1 at most: the dense solve)
   int nu1, nu2;
+  int q;     // cells of the top level per thread (2 to 5)
   double wj;
   BottomLevel lv[BOTTOM_MAX_LEVELS];
   const int* cmap;  // padded indices of the coarsest active cells
   const int* ncount;
   const double* ainv;
-  int max_n;
+  int nco, max_n;
+  // the coarsest level's inverse, transposed, in the compute type; in LDS (at
+  // bmat) or, when it does not fit or has more than 64 rows, read from memory
+  void* mat;
+  int mat_lds, bmat;
   int bcidx;       // LDS byte offset of the coarsest cells' compact indices
-  int zero_bytes;  // leading LDS bytes (iterates, right-hand sides) cleared per launch
+  int const_off;   // LDS byte offset and bytes of the constants
+  int const_bytes;
   size_t lds_bytes;
-  const void* img;  // LDS bytes [zero_bytes, lds_bytes) as built by launch_bottom_image
+  // the constants in global memory: those of the top level (per cell: three
+  // words of neighbour indices and the parent word; six face coefficients;
+  // wj / D) and the LDS bytes [const_off, const_off + const_bytes)
+  const uint32_t* top_nb;   // [4][n]
+  const float* top_cf;      // [6][n]
+  const void* top_wd;       // [n], compute type
+  const void* img;
 };
+// Builds the constants on the device, once per grid.
 template <class C>
-void launch_bottom_image(const Bottom& B, void* img, hipStream_t s);
+void launch_bottom_setup(const Bottom& B, hipStream_t s);
 template <class SC, class C>
 size_t bottom_lds_limit();
 template <class SC, class C>
