@@ -417,7 +417,7 @@ enum {
   NFVM_K_BOTTOM = 13,      /* LDS bottom solver, or the coarsest dense solve */
   NFVM_K_FCG_START = 14,   /* r = b - A x0, ||b||, ||r|| and level 0's first sweep */
   NFVM_K_FINALIZE = 15,    /* one-workgroup finalisers of the reductions */
-  NFVM_K_SMOOTH0_PAIR = 16, /* two damped-Jacobi sweeps in one pass on level 0 */
+  NFVM_K_SMOOTH0_PAIR = 16, /* two or three damped-Jacobi sweeps in one pass on level 0 */
   NFVM_K_COUNT = 17
 };
 nfvm_status nfvm_profile(nfvm_grid_t grid, uint32_t kernel_mask);
@@ -487,8 +487,11 @@ nfvm_status nfvm_profile_read(nfvm_grid_t grid, int32_t kernel, int64_t* launche
  *                     multiple of 4 cells, as many as keep the V-cycle's
  *                     result out of the buffer the next cycle's first sweep
  *                     is fused into; the fields are bitwise those of single
- *                     sweeps.  0: one sweep per pass.  Batched iterations
- *                     (nfvm_step_batch, serving) take single sweeps.
+ *                     sweeps.  On small grids (131072 cells) up to three
+ *                     run in one pass, with the transfer next to them, in
+ *                     batched iterations (nfvm_step_batch, serving) too;
+ *                     on larger ones those take single sweeps.  0: one
+ *                     sweep per pass.
  *                     Other values: NFVM_E_INVAL.
  * Errors: NFVM_E_INVAL for an unknown option. */
 enum {

@@ -424,8 +424,6 @@ class GridT : public GridBase {
       prof_bytes[NFVM_K_RHS] = N * (3 * sv + so + 1);
       prof_bytes[NFVM_K_PROJECT] = N * (6 * sv + 2 * sp + so + 1);
       prof_bytes[NFVM_K_FCG_APPLY] = N * (2 * s0 + so + 2);
-      // (x is read and written every other iteration)
-      prof_bytes[NFVM_K_FCG_UPDATE] = N * (5 * s0 + 3 * so + 2);
     }
     NFVM_CK(hipEventCreate(&ev0));
     NFVM_CK(hipEventCreate(&ev1));
@@ -1056,7 +1054,7 @@ class GridT : public GridBase {
     const double sf = elem_size(l), sc = elem_size(l + 1);
     return nf * (2 * sf + 1) + nc * (sc + 1);
   }
-  // the bottom solver: its top level's b read and x written, the constant
+  // the bottom solver: its top level's b read and x written, its
   // constants and its matrix read; the coarsest dense solve: the inverse and its vectors
   double bottom_bytes_moved() const {
     const double nt = (double)lv[bottom_top].g.cells(), sc = elem_size(bottom_top);
@@ -1071,6 +1069,12 @@ class GridT : public GridBase {
   double start_bytes(bool have_x0) const {
     const double N = (double)ncells, so = sizeof(O), s0 = sizeof(S0);
     return N * ((have_x0 ? 4 : 3) * so + 2 + (zero0() ? 2 : 1) * s0);
+  }
+  // CG update: z, the direction and its predecessor, r, x every other
+  // iteration, the level-0 right-hand side and (fused) first sweep
+  double update_bytes() const {
+    const double s0 = sizeof(S0);
+    return (double)ncells * ((zero0() ? 5 : 4) * s0 + 3 * sizeof(O) + 2);
   }
   int n_coarse = 0;  // active cells of the coarsest level
 
@@ -1210,7 +1214,14 @@ class GridT : public GridBase {
   // result z around every cell while it writes level 0's fused sweep; with
   // nu1 + nu2 odd the sweeps leave z in the buffer that sweep goes to, so
   // level 0 then sweeps from zero itself.
-  bool fused_zero(int l) const {
+  // Chain levels form their first sweep themselves.
+  bool chained(int l) const {
+    return l != bottom_top && l < L - 1 &&
+           (l > 0 || use_pairs) &&
+           chain_level(lv[l], pre_of(l), post_of(l), lv[l].g.cells());
+  }
+  bool fused_zero(int l) const { return !chained(l) && fusable_zero(l); }
+  bool fusable_zero(int l) const {
     return pre_of(l) > 0 && l != bottom_top && l < L - 1 && (l > 0 || (nu1 + nu2) % 2 == 0);
   }
   void* zero_of(int l) const { return fused_zero(l) ? lv[l].x[0] : nullptr; }
@@ -1235,6 +1246,13 @@ class GridT : public GridBase {
         launch_coarse_solve<decltype(t), C>(v, cmap, ncount, work, COARSE_MAX, red.out, stream);
       });
       prof_end(NFVM_K_BOTTOM);
+      return;
+    }
+    if (chained(l)) {
+      v.cur = 0;
+      chain(l, true);
+      vcycle(l + 1);
+      chain(l, false);
       return;
     }
     if (pre_of(l) > 0) {
@@ -1277,6 +1295,33 @@ class GridT : public GridBase {
       prof_end(NFVM_K_PROLONG_C);
     }
     sweeps(l, post_of(l), false);
+  }
+
+  // the launches of a chain level before (down) or after the coarse correction
+  void chain(int l, bool down) {
+    ChainStep st[CHAIN_STEPS];
+    const int m = chain_split(down ? pre_of(l) : post_of(l), down, st);
+    for (int q = 0; q < m; ++q) {
+      // x (unless from zero), b and the class or face code in, x out; the
+      // transfer's coarse side
+      const double nf = (double)lv[l].g.cells(), sf = elem_size(l);
+      double bytes = nf * ((st[q].zero ? 2 : 3) * sf + (l == 0 ? 2 : 1));
+      if (st[q].restr || st[q].pro)
+        bytes += (double)lv[l + 1].g.cells() * (elem_size(l + 1) + 1);
+      const int kid = l == 0 && st[q].nsw >= 2 ? NFVM_K_SMOOTH0_PAIR
+                      : st[q].restr            ? (l ? NFVM_K_RESTRICT_C : NFVM_K_RESTRICT0)
+                      : st[q].pro              ? (l ? NFVM_K_PROLONG_C : NFVM_K_PROLONG0)
+                                               : (l ? NFVM_K_SMOOTH_C : NFVM_K_SMOOTH0);
+      prof_begin(kid, bytes);
+      as_level(l, [&](auto f) {
+        as_level(l + 1, [&](auto c) {
+          launch_chain<decltype(f), C, decltype(c)>(lv[l], lv[l + 1], st[q], wj, red.out,
+                                                    zero_of(l + 1), stream);
+        });
+      });
+      prof_end(kid);
+      lv[l].cur ^= 1;
+    }
   }
 
   // Two-sweep passes on level 0 in this V-cycle: before and after the coarse
@@ -1330,7 +1375,7 @@ class GridT : public GridBase {
     prof_begin(NFVM_K_FCG_APPLY);
     launch_fcg_apply<O, S0>(lv[0], r, dir, red, stream);
     prof_end(NFVM_K_FCG_APPLY);
-    prof_begin(NFVM_K_FCG_UPDATE);
+    prof_begin(NFVM_K_FCG_UPDATE, update_bytes());
     launch_fcg_update<O, S0>(lv[0], phi, r, dir, red, stream, true, zero0(), wj);
     prof_end(NFVM_K_FCG_UPDATE);
   }
@@ -1820,7 +1865,10 @@ class GridT : public GridBase {
     d.ncount = ncount;
     d.ainv = work;
     d.coarse_max = COARSE_MAX;
-    for (int l = 0; l < L; ++l) d.zero[l] = zero_of(l);
+    // (which coarse levels are chained depends on the batch; level 0 is as it
+    // is alone: the CG kernels that write its first sweep may run elsewhere)
+    d.chain0 = chained(0);
+    for (int l = 0; l < L; ++l) d.zero[l] = fusable_zero(l) ? lv[l].x[0] : nullptr;
     d.red = red;
     d.x = phi;
     d.r = r;

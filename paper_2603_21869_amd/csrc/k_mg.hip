@@ -185,6 +185,15 @@ __device__ __forceinline__ void apply_at(const LevelView& L, uint8_t cl, const S
   D = g.sd > 0.0 ? (C)g.sd : d;
 }
 
+// q = n / d for 0 <= n < 2^22 from a float reciprocal of d, corrected to the
+// exact integer quotient.
+__device__ __forceinline__ int qdiv(int n, int d, float inv) {
+  int q = (int)((float)n * inv);
+  const int r = n - q * d;
+  q += (r >= d) - (r < 0);
+  return q;
+}
+
 // Tiles of a level for the column-walking kernels below.
 __host__ inline Tiles lvl_tiles(const Level& l, int kid) {
   return make_tiles(l.g.nx, l.g.ny, l.g.nz, l.tt[kid]);
@@ -1421,6 +1430,407 @@ __device__ __forceinline__ void prolong_nearest_body(const ProlongArgs<S, C, SC>
 NFVM_TILE_KERNELS(k_prolong_nearest, prolong_nearest_body, ProlongArgs, (S, C, SC),
                   (class S, class C, class SC), (S, C, SC), MBS, false)
 
+// ---- several operators of a small level in one launch -----------------------------
+// On a level of a few ten thousand cells a launch costs its latency, 4 to 6 us
+// with its gap whatever its work, and a V-cycle makes five or more per level.
+// A chain launch runs some of them in a row: the correction from the next
+// coarser level (PRO) or the first sweep from zero (ZERO), NSW damped-Jacobi
+// sweeps, and with RESTR the residual and its restriction.  Each workgroup owns
+// a box of cells and loads it once with a halo of H = NSW + RESTR cells (the
+// correction and the first sweep are formed on the halo too); sweep s is formed
+// on the cells at least s away from the halo's outside, and only the box's own
+// cells are stored.  Between the operators a value is rounded to the level's
+// storage type as a store rounds it, and every value takes the operations of
+// the single launches in their order, so the results are bitwise theirs.  The
+// halo's cells are formed again by several workgroups, which find idle compute
+// units on these levels.  Bound by latency: one round of loads, then LDS and a
+// barrier per sweep.  Measured on 16384 FP64 cells: the first sweep, a sweep
+// and the restriction 7 us against 4.6 + 6.4 in single launches (the first
+// sweep rides on the level above's restriction there), the correction and two
+// sweeps 8 us against 5.5 + 2 x 4.6.
+constexpr int CH_THREADS = 512, CH_SLOTS = 4, CH_MAX = CH_THREADS * CH_SLOTS;
+constexpr int CH_COARSE = 1152;  // coarse cells under a loaded box, at most
+template <class S, class C, class SC>
+struct ChainArgs {
+  LevelView F;
+  Tiles T;          // boxes (T.cz: not used)
+  int bx, by, bz;   // box edges (even)
+  float inx, inxy;  // reciprocals of the loaded box's row and plane
+  const S* x;       // (not read with zero)
+  S* xout;
+  const S* b;
+  C wj;
+  const double* ctl;
+  int zero, pro;
+  LevelView Cl;  // the next coarser level
+  const SC* e;   // pro: its iterate
+  SC* bc;        // RESTR: its right-hand side
+  SC* zc;        // ... and first sweep from zero (null: not fused)
+  int cx, cy, cz;        // pro: coarse cells under the loaded box
+  float icx, icxy;
+};
+
+// v as the storage type holds it
+template <class S, class C>
+__device__ __forceinline__ C stored(C v) {
+  S s;
+  St<S, C>::st(&s, v);
+  return St<S, C>::ld(&s);
+}
+
+// The operator at one cell of a level: level 0 from its face code, coarse
+// levels from the class byte and face coefficients.
+template <class C, bool CODE>
+struct ChainCell;
+template <class C>
+struct ChainCell<C, true> {
+  uint32_t cd;
+  __device__ void none() { cd = FACE_CODE_INACTIVE; }
+  __device__ void load(const LevelView& L, int P) { cd = L.code[P]; }
+  __device__ bool active() const { return cd != FACE_CODE_INACTIVE; }
+  __device__ C diag(const Geom& g) const { return diag_code<C>(g, cd); }
+  __device__ C sweep(const Geom& g, const JacobiConst<C>& jk, C xP, C xl, C xh, C xs, C xn, C xm,
+                     C xp, C bP) const {
+    return jacobi_code<C>(g, jk, cd, xP, xl, xh, xs, xn, xm, xp, bP);
+  }
+  __device__ C resid(const Geom& g, C xP, C xl, C xh, C xs, C xn, C xm, C xp, C bP) const {
+    C A, D;
+    apply_code_v<C>(g, cd, xP, xl, xh, xs, xn, xm, xp, A, D);
+    return bP - A;
+  }
+};
+template <class C>
+struct ChainCell<C, false> {
+  uint8_t cl;
+  Nbhd<C> n;
+  __device__ void none() { cl = MG_INACTIVE; }
+  __device__ void load(const LevelView& L, int P) {
+    cl = L.cls[P];
+    load_coef<C>(L, P, n);
+  }
+  __device__ bool active() const { return cl != MG_INACTIVE; }
+  __device__ C diag(const Geom& g) const { return diag_cls<C>(g, cl == MG_REGULAR, n); }
+  __device__ Nbhd<C> with(C xl, C xh, C xs, C xn) const {
+    Nbhd<C> m = n;
+    m.xl = xl;
+    m.xh = xh;
+    m.xs = xs;
+    m.xn = xn;
+    return m;
+  }
+  __device__ C sweep(const Geom& g, const JacobiConst<C>& jk, C xP, C xl, C xh, C xs, C xn, C xm,
+                     C xp, C bP) const {
+    const bool reg = cl == MG_REGULAR;
+    const Nbhd<C> m = with(xl, xh, xs, xn);
+    const C D = diag_cls<C>(g, reg, m);
+    return xP + jk.wj * (bP - apply_cls<C>(g, reg, m, xP, xm, xp)) / D;
+  }
+  __device__ C resid(const Geom& g, C xP, C xl, C xh, C xs, C xn, C xm, C xp, C bP) const {
+    return bP - apply_cls<C>(g, cl == MG_REGULAR, with(xl, xh, xs, xn), xP, xm, xp);
+  }
+};
+
+template <class S, class C, class SC, bool CODE, int NSW, bool RESTR>
+__device__ __forceinline__ void chain_body(const ChainArgs<S, C, SC>& a, const TileCtx& c, bool) {
+  constexpr int H = NSW + (RESTR ? 1 : 0), NT = CH_THREADS, Q = CH_SLOTS;
+  __shared__ C lx[2][CH_MAX];
+  const bool done = a.ctl[S_DONE] != 0.0;
+  const LevelView& L = a.F;
+  const Geom& g = L.g;
+  const bool d3 = g.dim == 3;
+  const int t = threadIdx.x;
+  const int ex = a.bx + 2 * H, ey = a.by + 2 * H, ez = d3 ? a.bz + 2 * H : 1;
+  const int exy = ex * ey, nE = exy * ez;
+  const int i0 = c.tx * a.bx - H, j0 = c.ty * a.by - H, k0 = d3 ? c.tz * a.bz - H : 0;
+  const JacobiConst<C> jk = jacobi_const<C>(g, a.wj);
+  int P[Q], mg[Q];
+  C xv[Q], bv[Q];
+  ChainCell<C, CODE> cell[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int e = t + q * NT;
+    mg[q] = -1;  // (distance to the outside of the halo)
+    cell[q].none();
+    xv[q] = bv[q] = (C)0;
+    P[q] = 0;
+    if (e >= nE) continue;
+    const int kz = qdiv(e, exy, a.inxy), r = e - kz * exy;
+    const int ky = qdiv(r, ex, a.inx), kx = r - ky * ex;
+    mg[q] = min(min(kx, ex - 1 - kx), min(ky, ey - 1 - ky));
+    if (d3) mg[q] = min(mg[q], min(kz, ez - 1 - kz));
+    const int i = i0 + kx, j = j0 + ky, k = k0 + kz;
+    if (i >= 0 && i < g.nx && j >= 0 && j < g.ny && k >= 0 && k < g.nz) {
+      P[q] = g.idx(i, j, k);
+      cell[q].load(L, P[q]);
+      if (!a.zero) xv[q] = St<S, C>::ld(a.x + P[q]);
+      bv[q] = St<S, C>::ld(a.b + P[q]);
+    }
+  }
+  if constexpr (!RESTR) {
+    // the correction: the coarse cells under the loaded box through LDS, then
+    // the rules of prolong_body at every loaded cell
+    __shared__ C le[CH_COARSE];
+    __shared__ float lf[3][CH_COARSE];
+    __shared__ uint8_t la[CH_COARSE];
+    if (a.pro) {
+      const LevelView& K = a.Cl;
+      const Geom& cg = K.g;
+      const int I0 = (i0 >> 1) - 1, J0 = (j0 >> 1) - 1, K0 = d3 ? (k0 >> 1) - 1 : 0;
+      const int cxy = a.cx * a.cy, nc = cxy * a.cz;
+      for (int w = t; w < nc; w += NT) {
+        const int wz = qdiv(w, cxy, a.icxy), r = w - wz * cxy;
+        const int wy = qdiv(r, a.cx, a.icx), wx = r - wy * a.cx;
+        const int I = I0 + wx, J = J0 + wy, Kz = K0 + wz;
+        C v = 0;
+        float f0 = 0, f1 = 0, f2 = 0;
+        uint8_t ac = 0;
+        // (the padded arrays hold one ghost layer around the box)
+        if (I >= -1 && I <= cg.nx && J >= -1 && J <= cg.ny &&
+            (d3 ? Kz >= -1 && Kz <= cg.nz : true)) {
+          const int Qc = cg.idx(I, J, Kz);
+          v = St<SC, C>::ld(a.e + Qc);
+          ac = K.cls[Qc] != MG_INACTIVE;
+          f0 = K.cf0[Qc];
+          f1 = K.cf1[Qc];
+          f2 = d3 ? K.cf2[Qc] : 0.f;
+        }
+        le[w] = v;
+        lf[0][w] = f0;
+        lf[1][w] = f1;
+        lf[2][w] = f2;
+        la[w] = ac;
+      }
+      if (done) return;  // (uniform, before the first barrier)
+      __syncthreads();
+      const C w3 = (C)0.75, w1 = (C)0.25;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (!cell[q].active()) continue;
+        const int e = t + q * NT;
+        const int kz = qdiv(e, exy, a.inxy), r = e - kz * exy;
+        const int ky = qdiv(r, ex, a.inx), kx = r - ky * ex;
+        const int i = i0 + kx, j = j0 + ky, k = k0 + kz;
+        const int I = i >> 1, J = j >> 1, Kz = d3 ? k >> 1 : 0;
+        const int sx = (i & 1) ? 1 : -1, sy = (j & 1) ? 1 : -1, sz = (k & 1) ? 1 : -1;
+        const int oy = sy * a.cx, oz = sz * cxy;
+        const bool inx = (unsigned)(I + sx) < (unsigned)cg.nx;
+        const bool iny = (unsigned)(J + sy) < (unsigned)cg.ny;
+        const int W = (Kz - K0) * cxy + (J - J0) * a.cx + (I - I0);
+        // the plane value of plane_rules at the coarse cell at W
+        auto plane = [&](int V, bool in_plane, C& Y, bool& act) {
+          plane_value<C>(le[V], le[V + sx], le[V + oy], le[V + oy + sx], in_plane && la[V],
+                         la[V + sx] != 0, iny && in_plane && la[V + oy], la[V + oy + sx] != 0,
+                         (C)lf[0][sx > 0 ? V + 1 : V], (C)lf[0][sx > 0 ? V + oy + 1 : V + oy],
+                         (C)lf[1][oy > 0 ? V + oy : V], inx, iny, Y, act);
+        };
+        C Y;
+        bool ac;
+        plane(W, true, Y, ac);
+        C Z = Y;
+        if (d3) {
+          const bool inz = (unsigned)(Kz + sz) < (unsigned)cg.nz;
+          C Yn = 0;
+          bool an = false;
+          plane(W + oz, inz, Yn, an);
+          const C cfz = (C)lf[2][sz > 0 ? W + oz : W];
+          const C zn = inz ? (an ? Yn : Y) : ((C)1 - cfz) * Y;
+          Z = w3 * Y + w1 * zn;
+        }
+        xv[q] = stored<S, C>(xv[q] + Z);
+      }
+    }
+  }
+  if (done) return;  // (uniform; with the correction tested above)
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (a.zero && cell[q].active()) xv[q] = stored<S, C>(a.wj * bv[q] / cell[q].diag(g));
+    if (mg[q] >= 0) lx[0][t + q * NT] = xv[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 1; s <= NSW; ++s) {
+    const C* in = lx[(s - 1) & 1];
+    C* out = lx[s & 1];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (mg[q] < s) continue;
+      const int e = t + q * NT;
+      if (cell[q].active())
+        xv[q] = stored<S, C>(cell[q].sweep(g, jk, xv[q], in[e - 1], in[e + 1], in[e - ex],
+                                           in[e + ex], d3 ? in[e - exy] : (C)0,
+                                           d3 ? in[e + exy] : (C)0, bv[q]));
+      out[e] = xv[q];  // (inactive cells: 0)
+    }
+    __syncthreads();
+  }
+  const C* fin = lx[NSW & 1];
+  C* res = lx[(NSW + 1) & 1];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (mg[q] < H) continue;
+    const int e = t + q * NT;
+    const bool act = cell[q].active();
+    if (act) St<S, C>::st(a.xout + P[q], xv[q]);
+    if (RESTR)
+      res[e] = act ? cell[q].resid(g, xv[q], fin[e - 1], fin[e + 1], fin[e - ex], fin[e + ex],
+                                   d3 ? fin[e - exy] : (C)0, d3 ? fin[e + exy] : (C)0, bv[q])
+                   : (C)0;
+  }
+  if (!RESTR) return;
+  __syncthreads();
+  // the restriction, summed as restrict_body sums it
+  const Geom& cg = a.Cl.g;
+  const int hx = a.bx / 2, hy = a.by / 2, hz = d3 ? a.bz / 2 : 1;
+  for (int w = t; w < hx * hy * hz; w += NT) {
+    const int wi = w % hx, wr = w / hx, wy = wr % hy, wk = wr / hy;
+    const int I = c.tx * hx + wi, J = c.ty * hy + wy, K = d3 ? c.tz * hz + wk : 0;
+    if (I >= cg.nx || J >= cg.ny || K >= cg.nz) continue;
+    const int PC = cg.idx(I, J, K);
+    const uint8_t ccl = a.Cl.cls[PC];
+    if (ccl == MG_INACTIVE) continue;
+    const C* r = res + (d3 ? (H + 2 * wk) * exy : 0) + (H + 2 * wy) * ex + H + 2 * wi;
+    C s0 = r[0], s1 = r[1], u0 = r[ex], u1 = r[ex + 1];
+    if (d3) {
+      s0 += r[exy];
+      s1 += r[exy + 1];
+      u0 += r[exy + ex];
+      u1 += r[exy + ex + 1];
+    }
+    const C bc = ((s0 + s1) + (u0 + u1)) * (C)(d3 ? 0.125 : 0.25);
+    St<SC, C>::st(a.bc + PC, bc);
+    if (a.zc) St<SC, C>::st(a.zc + PC, zero_sweep_of<SC, C>(bc, a.wj, diag_at<C>(a.Cl, ccl, PC)));
+  }
+}
+NFVM_TILE_KERNELS(k_chain, chain_body, ChainArgs, (S, C, SC),
+                  (class S, class C, class SC, bool CODE, int NSW, bool RESTR),
+                  (S, C, SC, CODE, NSW, RESTR), CH_THREADS, false)
+
+// Whether level l (pre and post sweeps) takes them; cells: of the level's
+// launch, with those of the grids batched with it (level 0: its own).  Past the limits the halo's extra work costs more than the saved
+// launches.  Measured per iteration without / with, FP64, two sweeps on each
+// side: level 0 of 32768 cells 68.9 / 51.1 us, 131072 76.7 / 70.2, 262144
+// 89.8 / 85.3, 393216 104.8 / 108.4; level 1 of 32768 cells 90.2 / 85.5,
+// 131072 134.5 / 133.1, 262144 188.2 / 188.3 (FP32 with three sweeps: slower).
+// Per step of 8 batched grids: level 1 of 8 x 32768 cells 650 / 623 us, level
+// 0 of 8 x 131072 438 / 432, of 8 x 262144 645 / 650.  Levels without
+// smoothing on one side and Algorithm 1's literal form keep the single launches.
+constexpr long long CHAIN_CELLS = 1 << 17;
+bool chain_level(const Level& l, int pre, int post, long long cells) {
+  return pre >= 1 && post >= 1 && pre <= CHAIN_STEPS && post <= CHAIN_STEPS && l.g.sd == 0.0 &&
+         !l.nearest && l.g.cells() <= CHAIN_CELLS && cells <= 2 * CHAIN_CELLS;
+}
+
+// The launches before (down) or after the coarse correction, in order: at most
+// three sweeps each, with the restriction at most two before it.
+int chain_split(int sweeps, bool down, ChainStep (&st)[CHAIN_STEPS]) {
+  int m = 0;
+  const int n = down ? sweeps - 1 : sweeps;  // (the first one starts from zero)
+  const int last = !down ? 0 : (n == 2 || n >= 4 ? 2 : (n > 0 ? 1 : 0));
+  for (int left = n - last; left > 0;) {
+    const int launches = (left + 2) / 3, k = (left + launches - 1) / launches;
+    st[m++] = ChainStep{k, false, false, false};
+    left -= k;
+  }
+  if (down) st[m++] = ChainStep{last, true, false, false};
+  if (m > 0) (down ? st[0].zero : st[0].pro) = true;
+  return m;
+}
+
+// coarse cells under b + 2 h fine ones (b even) with a neighbour on each side
+static int chain_under(int b, int h) { return ((b + h - 1) >> 1) - ((-h) >> 1) + 3; }
+
+// The box of a launch with a halo of h cells, for `share` grids of its size in
+// the launch: of the shapes that fit the slots and the LDS, the one of the
+// shortest time on 256 CUs by a count of 2 us for a workgroup's loads and
+// 0.35 us for each pass over its slots.  (8 grids of 32768 FP64 cells with the
+// box that suits one of them: 30.6 us a launch against 16.1.)
+static void chain_box(const Geom& g, int h, int share, int& bx, int& by, int& bz) {
+  const bool d3 = g.dim == 3;
+  double best = 1e300;
+  for (int x = 4; x <= 32; x *= 2)
+    for (int y = 2; y <= 16; y *= 2)
+      for (int z = d3 ? 2 : 1; z <= (d3 ? 16 : 1); z *= 2) {
+        const int e = (x + 2 * h) * (y + 2 * h) * (d3 ? z + 2 * h : 1);
+        const int cc = chain_under(x, h) * chain_under(y, h) * (d3 ? chain_under(z, h) : 1);
+        if (e > CH_MAX || cc > CH_COARSE) continue;
+        const long long w = (long long)((g.nx + x - 1) / x) * ((g.ny + y - 1) / y) *
+                            ((g.nz + z - 1) / z) * share;
+        const int slots = (e + CH_THREADS - 1) / CH_THREADS;
+        const double t = (double)((w + 255) / 256) * (2.0 + 0.35 * (h + 1) * slots) +
+                         1e-4 * (double)e + 1e-6 * (double)w;
+        if (t < best) {
+          best = t;
+          bx = x;
+          by = y;
+          bz = z;
+        }
+      }
+}
+
+template <class S, class C, class SC>
+ChainArgs<S, C, SC> chain_args(const Level& f, const Level& c, const ChainStep& st, double wj,
+                               const double* ctl, void* zc, int share) {
+  ChainArgs<S, C, SC> a;
+  memset(&a, 0, sizeof a);
+  const int h = st.nsw + (st.restr ? 1 : 0);
+  const bool d3 = f.g.dim == 3;
+  a.F = view(f);
+  chain_box(f.g, h, share, a.bx, a.by, a.bz);
+  a.T.ntx = (f.g.nx + a.bx - 1) / a.bx;
+  a.T.nty = (f.g.ny + a.by - 1) / a.by;
+  a.T.ntz = (f.g.nz + a.bz - 1) / a.bz;
+  a.T.cz = 1;
+  a.T.total = a.T.ntx * a.T.nty * a.T.ntz;
+  a.T.grid = (a.T.total + 7) / 8 * 8;
+  a.inx = 1.0f / (float)(a.bx + 2 * h);
+  a.inxy = 1.0f / (float)((a.bx + 2 * h) * (a.by + 2 * h));
+  a.x = (const S*)f.x[f.cur];
+  a.xout = (S*)f.x[f.cur ^ 1];
+  a.b = (const S*)f.b;
+  a.wj = (C)wj;
+  a.ctl = ctl;
+  a.zero = st.zero;
+  a.pro = st.pro;
+  a.Cl = view(c);
+  a.e = (const SC*)c.x[c.cur];
+  a.bc = (SC*)c.b;
+  a.zc = (SC*)zc;
+  a.cx = chain_under(a.bx, h);
+  a.cy = chain_under(a.by, h);
+  a.cz = d3 ? chain_under(a.bz, h) : 1;
+  a.icx = 1.0f / (float)a.cx;
+  a.icxy = 1.0f / (float)(a.cx * a.cy);
+  return a;
+}
+
+// Calls fn with the step's sweeps and restriction as constants.
+template <class F>
+void chain_as(const ChainStep& st, F&& fn) {
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, 2> I2;
+  typedef std::integral_constant<int, 3> I3;
+  if (st.restr)
+    st.nsw == 0 ? fn(I0(), I1()) : st.nsw == 1 ? fn(I1(), I1()) : fn(I2(), I1());
+  else
+    st.nsw == 1 ? fn(I1(), I0()) : st.nsw == 2 ? fn(I2(), I0()) : fn(I3(), I0());
+}
+
+template <class S, class C, class SC>
+void launch_chain(const Level& f, const Level& c, const ChainStep& st, double wj,
+                  const double* ctl, void* zc, hipStream_t s) {
+  const auto a = chain_args<S, C, SC>(f, c, st, wj, ctl, zc, 1);
+  const dim3 G(a.T.grid), B(CH_THREADS);
+  chain_as(st, [&](auto n, auto r) {
+    constexpr int N = decltype(n)::value;
+    constexpr bool R = decltype(r)::value != 0;
+    if (!f.code)
+      NFVM_LAUNCH((k_chain<S, C, SC, false, N, R>), G, B, 0, s, a);
+    else if constexpr (has_quad<S>)
+      NFVM_LAUNCH((k_chain<S, C, SC, true, N, R>), G, B, 0, s, a);
+  });
+}
+
 // Whether the prolongation to fine level f takes the four-column kernel.
 __host__ inline bool prolong_quad(const Level& f) {
   return f.code && f.g.nx % 4 == 0 && !f.nearest;
@@ -2274,14 +2684,6 @@ void launch_finalize(int nv, int op, const RedBuf& red, int nblocks, int slot0, 
 // access into a flat one).
 extern __shared__ __align__(16) unsigned char bot_lds[];
 
-// q = n / d for 0 <= n < 2^22 from a float reciprocal of d, corrected to the
-// exact integer quotient.
-__device__ __forceinline__ int qdiv(int n, int d, float inv) {
-  int q = (int)((float)n * inv);
-  const int r = n - q * d;
-  q += (r >= d) - (r < 0);
-  return q;
-}
 __device__ __forceinline__ void lds_ijk(const BottomLevel& L, int c, int& i, int& j, int& k) {
   const int nxy = L.g.nx * L.g.ny;
   k = qdiv(c, nxy, L.inxy);
@@ -2967,11 +3369,12 @@ size_t put(BatchOps& o, const std::vector<V>& v) {
 // workgroups.  With pad, a grid's padding tiles are part of its range (its
 // reduction partials are all written).
 template <class A, class K1, class KB>
-void emit_tiles(BatchOps& o, const Group<A>& g, K1 single, KB batched, bool pad) {
+void emit_tiles(BatchOps& o, const Group<A>& g, K1 single, KB batched, bool pad,
+                dim3 block = dim3(MBX, MBY)) {
   if (g.size() == 1) {
     const A a = g[0];
     o.ops.push_back([=](const unsigned char*, hipStream_t s) {
-      hipLaunchKernelGGL(single, dim3(a.T.grid), dim3(MBX, MBY), 0, s, a);
+      hipLaunchKernelGGL(single, dim3(a.T.grid), block, 0, s, a);
     });
     return;
   }
@@ -2986,7 +3389,7 @@ void emit_tiles(BatchOps& o, const Group<A>& g, K1 single, KB batched, bool pad)
     }
     const int blocks = (p.start[p.n] + 7) / 8 * 8;
     o.ops.push_back([=](const unsigned char*, hipStream_t s) {
-      hipLaunchKernelGGL(batched, dim3(blocks), dim3(MBX, MBY), 0, s, p);
+      hipLaunchKernelGGL(batched, dim3(blocks), block, 0, s, p);
     });
   }
 }
@@ -3107,7 +3510,7 @@ void emit_bottoms(BatchOps& o, const std::vector<BottomArgsBase>& bo, size_t lds
 template <class A, class B, class C>
 struct RestrictSet {
   Group<RestrictArgs<A, C, B>> plain, quad;
-  void add(const MgGridDesc& d, int l) {
+  void add(MgGridDesc& d, int l) {
     (restrict_quad(d.lv[l]) ? quad : plain)
         .push_back(restrict_args<A, C, B>(d.lv[l], d.lv[l + 1], d.red.out, d.zero[l + 1], d.wj));
   }
@@ -3118,11 +3521,43 @@ struct RestrictSet {
   }
 };
 
+// Chain launches on a level of type A with the next coarser one of type B:
+// coarse levels and level 0, by sweeps and restriction.
+template <class A, class B, class C>
+struct ChainSet {
+  Group<ChainArgs<A, C, B>> g[2][4][2];
+  void add(MgGridDesc& d, int l, const ChainStep& st, int share) {
+    Level& v = d.lv[l];
+    g[v.code != nullptr][st.nsw][st.restr].push_back(
+        chain_args<A, C, B>(v, d.lv[l + 1], st, d.wj, d.red.out, d.zero[l + 1], share));
+    v.cur ^= 1;
+  }
+  template <bool CODE, int N, bool R>
+  void emit_one(BatchOps& o) const {
+    if constexpr (!CODE || has_quad<A>)
+      emit_tiles(o, g[CODE][N][R], k_chain<A, C, B, CODE, N, R>,
+                 k_chain_batch<A, C, B, CODE, N, R>, false, dim3(CH_THREADS));
+  }
+  template <bool CODE>
+  void emit_level(BatchOps& o) const {
+    emit_one<CODE, 1, false>(o);
+    emit_one<CODE, 2, false>(o);
+    emit_one<CODE, 3, false>(o);
+    emit_one<CODE, 0, true>(o);
+    emit_one<CODE, 1, true>(o);
+    emit_one<CODE, 2, true>(o);
+  }
+  void emit(BatchOps& o) const {
+    emit_level<false>(o);
+    emit_level<true>(o);
+  }
+};
+
 // Prolongations to a level of type A from one of type B, by kernel.
 template <class A, class B, class C>
 struct ProlongSet {
   Group<ProlongArgs<A, C, B>> plain, quad, nearest;
-  void add(const MgGridDesc& d, int l) {
+  void add(MgGridDesc& d, int l) {
     (d.lv[l].nearest ? nearest : prolong_quad(d.lv[l]) ? quad : plain)
         .push_back(prolong_args<A, C, B>(d.lv[l], d.lv[l + 1], d.red.out));
   }
@@ -3142,16 +3577,17 @@ struct TypePairs {
   Set<W, N, C> wn;
   Set<N, N, C> nn;
   Set<N, W, C> nw;
-  void add(const MgGridDesc& d, int l) {
+  template <class... X>
+  void add(MgGridDesc& d, int l, const X&... x) {
     const bool a = wide_of(d, l), b = wide_of(d, l + 1);
     if (a && b)
-      ww.add(d, l);
+      ww.add(d, l, x...);
     else if (a)
-      wn.add(d, l);
+      wn.add(d, l, x...);
     else if (b)
-      nw.add(d, l);
+      nw.add(d, l, x...);
     else
-      nn.add(d, l);
+      nn.add(d, l, x...);
   }
   void emit(BatchOps& o) const {
     ww.emit(o);
@@ -3191,13 +3627,42 @@ void plan_fcg_iteration(MgGridDesc* G, int n, BatchOps& o) {
         launch_fill_zero<SC>(lv, lv.x[0], ctl, s);
     });
   };
+  // which levels of which grids take chain launches (a coarse level by the
+  // cells of its whole launch)
+  std::vector<std::vector<char>> chained(n, std::vector<char>(top + 1, 0));
+  for (int l = 0; l < top; ++l) {
+    long long cells = 0;
+    for (int i = 0; i < n; ++i)
+      if (l < stop_level(G[i])) cells += G[i].lv[l].g.cells();
+    for (int i = 0; i < n; ++i) {
+      if (l >= stop_level(G[i])) continue;
+      chained[i][l] = l == 0 ? G[i].chain0
+                             : chain_level(G[i].lv[l], pre_of(G[i], l), post_of(G[i], l), cells);
+      if (chained[i][l]) G[i].zero[l] = nullptr;  // (formed by the chain itself)
+    }
+  }
+  // one step of the chain launches of level l
+  auto chain_step = [&](int l, bool down, int q) {
+    TypePairs<ChainSet, S0, SC, C> cs;
+    int share = 0;
+    for (int i = 0; i < n; ++i) share += chained[i][l];
+    share = std::min(share, MAXB);
+    for (int i = 0; i < n; ++i) {
+      if (l >= stop_level(G[i]) || !chained[i][l]) continue;
+      ChainStep st[CHAIN_STEPS];
+      if (down && q == 0) G[i].lv[l].cur = 0;
+      if (q < chain_split(down ? pre_of(G[i], l) : post_of(G[i], l), down, st))
+        cs.add(G[i], l, st[q], share);
+    }
+    cs.emit(o);
+  };
   // down: pre-smoothing and restriction, level by level
   for (int l = 0; l < top; ++l) {
     for (int s = 0; s < std::max(max_pre(l), 1); ++s) {
       SweepGroups<S0, C> g0;
       SweepGroups<SC, C> gc;
       for (int i = 0; i < n; ++i) {
-        if (l >= stop_level(G[i])) continue;
+        if (l >= stop_level(G[i]) || chained[i][l]) continue;
         if (pre_of(G[i], l) == 0) {
           if (s == 0) fill(G[i], l);
           continue;
@@ -3209,10 +3674,11 @@ void plan_fcg_iteration(MgGridDesc* G, int n, BatchOps& o) {
       }
       g0.emit(o);
       gc.emit(o);
+      chain_step(l, true, s);
     }
     TypePairs<RestrictSet, S0, SC, C> rs;
     for (int i = 0; i < n; ++i)
-      if (l < stop_level(G[i])) rs.add(G[i], l);
+      if (l < stop_level(G[i]) && !chained[i][l]) rs.add(G[i], l);
     rs.emit(o);
   }
   // bottom solver or coarsest solve of every grid
@@ -3248,13 +3714,13 @@ void plan_fcg_iteration(MgGridDesc* G, int n, BatchOps& o) {
   for (int l = top - 1; l >= 0; --l) {
     TypePairs<ProlongSet, S0, SC, C> ps;
     for (int i = 0; i < n; ++i)
-      if (l < stop_level(G[i])) ps.add(G[i], l);
+      if (l < stop_level(G[i]) && !chained[i][l]) ps.add(G[i], l);
     ps.emit(o);
     for (int s = 0; s < max_post(l); ++s) {
       SweepGroups<S0, C> g0;
       SweepGroups<SC, C> gc;
       for (int i = 0; i < n; ++i) {
-        if (l >= stop_level(G[i])) continue;
+        if (l >= stop_level(G[i]) || chained[i][l]) continue;
         if (wide_of(G[i], l))
           add_sweep(g0, G[i], l, s, false);
         else
@@ -3262,6 +3728,7 @@ void plan_fcg_iteration(MgGridDesc* G, int n, BatchOps& o) {
       }
       g0.emit(o);
       gc.emit(o);
+      chain_step(l, false, s);
     }
   }
   // CG: the dot products with w = A z, then the vector update
@@ -3320,6 +3787,8 @@ template void launch_smooth2<float, float>(const Level&, const void*, void*, dou
                                            const double*, hipStream_t);
 
 #define INST_PAIR(S, C, SC)                                                                 \
+  template void launch_chain<S, C, SC>(const Level&, const Level&, const ChainStep&, double, \
+                                       const double*, void*, hipStream_t);                   \
   template void launch_resid_restrict<S, C, SC>(const Level&, const Level&, const double*,   \
                                                 hipStream_t, void*, double);                  \
   template void launch_prolong<S, C, SC>(const Level&, const Level&, const double*,          \

@@ -329,6 +329,19 @@ bool sweep_pair(const Level& l);
 template <class S, class C>
 void launch_smooth2(const Level& l, const void* xin, void* xout, double wj, const double* ctl,
                     hipStream_t s);
+// Several operators of a small level in one launch (chain_level): the
+// correction from the coarser level or the first sweep from zero, sweeps, the
+// residual's restriction.  Reads f.x[f.cur], writes f.x[f.cur ^ 1].
+struct ChainStep {
+  int nsw;
+  bool restr, zero, pro;
+};
+constexpr int CHAIN_STEPS = 64;  // most sweeps of a level (and so launches) they are used for
+bool chain_level(const Level& l, int pre, int post, long long cells);
+int chain_split(int sweeps, bool down, ChainStep (&st)[CHAIN_STEPS]);
+template <class S, class C, class SC>
+void launch_chain(const Level& f, const Level& c, const ChainStep& st, double wj,
+                  const double* ctl, void* zc, hipStream_t s);
 template <class S, class C, class SC>
 void launch_resid_restrict(const Level& f, const Level& c, const double* ctl, hipStream_t s,
                            void* zc = nullptr, double wj = 0.0);
@@ -430,7 +443,8 @@ struct MgGridDesc {
   const int* ncount;
   const double* ainv;
   int coarse_max;
-  void* zero[MAX_LEVELS];  // buffer of level l's fused first sweep, or null
+  void* zero[MAX_LEVELS];  // buffer of level l's fused first sweep, or null (chain levels: cleared)
+  bool chain0;             // level 0 takes chain launches
   RedBuf red;
   void *x, *r;
   void* dir[2];  // the two level-0 direction buffers (storage type of level 0)
