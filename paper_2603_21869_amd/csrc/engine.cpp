@@ -651,7 +651,10 @@ class GridT : public GridBase {
         });
         // the CG passes are timed with their finalising kernels (the block
         // count they sum grows with the tile count), on scratch scalars whose
-        // stopping rule never fires (forced count 1e30)
+        // stopping rule never fires (forced count 1e30); and on 64 x 4 tiles,
+        // whatever tiles they are launched with: the target chosen here sets
+        // the order of their sums, which is that of 64 x 4 tiles
+        v.tiles64 = true;
         RedBuf tr = red;
         tr.out = tune_out;
         tr.mirror = nullptr;
@@ -663,6 +666,7 @@ class GridT : public GridBase {
           v.tt[TK_UPDATE] = tt;
           launch_fcg_update<O, S0>(v, phi, r, dir, tr, stream, true, zero0(), wj);
         });
+        v.tiles64 = false;
       } else {
         // (the tuning key tells the storage types of the level and the next)
         const int tk = 1000 + (v.wide ? 2000 : 0) + (lv[l + 1].wide ? 4000 : 0);

@@ -199,6 +199,16 @@ __host__ inline Tiles lvl_tiles(const Level& l, int kid) {
   return make_tiles(l.g.nx, l.g.ny, l.g.nz, l.tt[kid]);
 }
 
+// Tiles of the kernels that take four x cells per thread (nq of them a row): on
+// short rows a wave covers 2, 4 or 8 rows instead of leaving the lanes past
+// the row's end idle.  (Batch of 8 grids of 64^3, where a row is 16 lanes:
+// the FP32 sweep 17.3 -> 7.7 us, the prolongation 18 -> 10.5, the
+// restriction 15 -> 8.4, the CG update 47 -> 22, its dot products 26 -> 11.5.)
+__host__ inline int quad_lw(int nq) { return nq <= 8 ? 3 : nq <= 16 ? 4 : nq <= 32 ? 5 : 6; }
+__host__ inline Tiles quad_tiles(int nq, int ny, int nz, int target_blocks) {
+  return make_tiles(nq, ny, nz, target_blocks, quad_lw(nq));
+}
+
 // ---- single and batched launches ----------------------------------------------------
 // Every level kernel is a body taking its arguments as one struct and the tile
 // it works on.  A single launch covers one grid (block b takes tile
@@ -208,11 +218,20 @@ __host__ inline Tiles lvl_tiles(const Level& l, int kid) {
 // the same partials in the same order.
 struct TileCtx {
   int tx, ty, tz, pb;
+  int i, j;  // this thread's column and row
 };
+
+__device__ __forceinline__ void tile_thread(const Tiles& T, TileCtx& c) {
+  const int t = threadIdx.y * MBX + threadIdx.x;
+  c.i = (c.tx << T.lw) + (t & ((1 << T.lw) - 1));
+  c.j = c.ty * (MBS >> T.lw) + (t >> T.lw);
+}
 
 __device__ __forceinline__ bool tile_single(const Tiles& T, TileCtx& c) {
   c.pb = blockIdx.x;
-  return tile_of(T, c.tx, c.ty, c.tz);
+  const bool v = tile_of(T, c.tx, c.ty, c.tz);
+  tile_thread(T, c);
+  return v;
 }
 
 __device__ __forceinline__ bool tile_of_index(const Tiles& T, int t, TileCtx& c) {
@@ -221,6 +240,7 @@ __device__ __forceinline__ bool tile_of_index(const Tiles& T, int t, TileCtx& c)
   c.tx = t % T.ntx;
   c.ty = (t / T.ntx) % T.nty;
   c.tz = t / (T.ntx * T.nty);
+  tile_thread(T, c);
   return t < T.total;
 }
 
@@ -569,7 +589,7 @@ __device__ __forceinline__ void smooth_code4_body(const SmoothArgs<S, C>& a, con
   const S* __restrict__ b = a.b;
   const C wj = a.wj;
   const Geom& g = L.g;
-  const int i0 = 4 * (c.tx * MBX + threadIdx.x), j = c.ty * MBY + threadIdx.y;
+  const int i0 = 4 * c.i, j = c.j;
   if (i0 >= g.nx || j >= g.ny) return;
   const int k0 = c.tz * a.T.cz, k1 = min(g.nz, k0 + a.T.cz);
   const bool d3 = g.dim == 3;
@@ -615,7 +635,7 @@ __device__ __forceinline__ void smooth4_body(const SmoothArgs<S, C>& a, const Ti
   const S* __restrict__ b = a.b;
   const C wj = a.wj;
   const Geom& g = L.g;
-  const int i0 = 4 * (c.tx * MBX + threadIdx.x), j = c.ty * MBY + threadIdx.y;
+  const int i0 = 4 * c.i, j = c.j;
   if (i0 >= g.nx || j >= g.ny) return;
   const int k0 = c.tz * a.T.cz, k1 = min(g.nz, k0 + a.T.cz);
   const bool d3 = g.dim == 3;
@@ -666,7 +686,7 @@ SmoothArgs<S, C> smooth_args(const Level& l, const void* xin, void* xout, double
                              const double* ctl) {
   const int tk = from_zero ? TK_SMOOTH_ZERO : TK_SMOOTH;
   const Tiles T = sweep_quad(l, from_zero) || coarse_quad<S>(l, from_zero)
-                      ? make_tiles(l.g.nx / 4, l.g.ny, l.g.nz, l.tt[tk])
+                      ? quad_tiles(l.g.nx / 4, l.g.ny, l.g.nz, l.tt[tk])
                       : lvl_tiles(l, tk);
   return SmoothArgs<S, C>{view(l), T, (const S*)xin, (S*)xout, (const S*)l.b, (C)wj, ctl};
 }
@@ -1009,7 +1029,7 @@ __device__ __forceinline__ void restrict4_body(const RestrictArgs<S, C, SC>& a, 
   const S* __restrict__ x = a.x;
   const S* __restrict__ b = a.b;
   const Geom& g = F.g;
-  const int i0 = 4 * (c.tx * MBX + threadIdx.x), J = c.ty * MBY + threadIdx.y;
+  const int i0 = 4 * c.i, J = c.j;
   if (i0 >= g.nx || J >= Cl.g.ny) return;
   const bool d3 = g.dim == 3;
   const int K0 = c.tz * a.T.cz, K1 = min(Cl.g.nz, K0 + a.T.cz);
@@ -1086,8 +1106,9 @@ template <class S, class C, class SC>
 RestrictArgs<S, C, SC> restrict_args(const Level& f, const Level& c, const double* ctl, void* zc,
                                      double wj) {
   return RestrictArgs<S, C, SC>{view(f),
-                                make_tiles(restrict_quad(f) ? f.g.nx / 4 : f.g.nx, c.g.ny,
-                                           c.g.nz, f.tt[TK_RESTRICT]),
+                                restrict_quad(f)
+                                    ? quad_tiles(f.g.nx / 4, c.g.ny, c.g.nz, f.tt[TK_RESTRICT])
+                                    : make_tiles(f.g.nx, c.g.ny, c.g.nz, f.tt[TK_RESTRICT]),
                                 (const S*)f.x[f.cur],
                                 (const S*)f.b,
                                 view(c),
@@ -1318,7 +1339,7 @@ __device__ __forceinline__ void prolong4_body(const ProlongArgs<S, C, SC>& a, co
   const LevelView& Cl = a.Cl;
   S* __restrict__ x = a.x;
   const SC* __restrict__ e = a.e;
-  const int i0 = 4 * (c.tx * MBX + threadIdx.x), j = c.ty * MBY + threadIdx.y;
+  const int i0 = 4 * c.i, j = c.j;
   if (i0 >= F.g.nx || j >= F.g.ny) return;
   const Geom& cg = Cl.g;
   const bool d3 = cg.dim == 3;
@@ -1842,7 +1863,8 @@ ProlongArgs<S, C, SC> prolong_args(const Level& f, const Level& c, const double*
   // coarse planes
   return ProlongArgs<S, C, SC>{
       view(f),
-      make_tiles(prolong_quad(f) ? f.g.nx / 4 : f.g.nx, f.g.ny, c.g.nz, f.tt[TK_PROLONG]),
+      prolong_quad(f) ? quad_tiles(f.g.nx / 4, f.g.ny, c.g.nz, f.tt[TK_PROLONG])
+                      : make_tiles(f.g.nx, f.g.ny, c.g.nz, f.tt[TK_PROLONG]),
       (S*)f.x[f.cur], view(c), (const SC*)c.x[c.cur], ctl};
 }
 
@@ -1929,6 +1951,45 @@ void launch_fill_zero(const Level& l, void* x, const double* ctl, hipStream_t s)
 // the stopping state live in red.out (ctl).  Every kernel walks column tiles
 // and writes one partial per workgroup (tiles outside the grid write zeros).
 
+// The four-cells-per-thread passes on short rows take tiles of 2, 4 or 8 times
+// four rows (quad_lw) and store the partial of every 64 x 4 tile in them: a
+// row is summed over its lanes and the rows of a 64 x 4 tile one after the
+// other, as block_partial sums them (the lanes it adds beyond the row's end
+// hold 0), so the partials and their order are those of 64 x 4 tiles.
+struct CgTiles {
+  int nb, total, nty;  // of the 64 x 4 tiles: partials, tiles, tile rows
+};
+template <int NV>
+__device__ __forceinline__ void cg_partial(double (&v)[NV], const RedBuf& red, const TileCtx& c,
+                                           const Tiles& T, const CgTiles& N, bool valid) {
+  if (T.lw == 6) {
+    block_partial<NV, R_SUM, MBS>(v, red, c.pb);
+    return;
+  }
+  __shared__ double sh[NV][MBS / 8];
+  const int t = threadIdx.y * MBX + threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < NV; ++q)
+    for (int off = (1 << T.lw) >> 1; off > 0; off >>= 1) v[q] += __shfl_xor(v[q], off);
+  if ((t & ((1 << T.lw) - 1)) == 0)
+    for (int q = 0; q < NV; ++q) sh[q][t >> T.lw] = v[q];
+  __syncthreads();
+  const int per = N.nb >> 3;
+  const int ty = (c.ty << (6 - T.lw)) + t;
+  if (valid && t < (64 >> T.lw) && ty < N.nty) {
+    const int o = c.tz * N.nty + ty, b = (o % per) * 8 + o / per;
+    for (int q = 0; q < NV; ++q) {
+      double acc = sh[q][4 * t];
+      for (int w = 1; w < 4; ++w) acc += sh[q][4 * t + w];
+      red.partial[(size_t)b * NV + q] = acc;
+    }
+  }
+  // (the partials past the last tile: 0)
+  if (valid && c.ty == 0 && c.tz == 0 && t < N.nb - N.total) {
+    const int o = N.total + t, b = (o % per) * 8 + o / per;
+    for (int q = 0; q < NV; ++q) red.partial[(size_t)b * NV + q] = 0.0;
+  }
+}
 // r = b - A x0 (x0 = 0 unless given), x = x0 on active cells, 0 elsewhere.
 // With z0 set, also the first sweep of the next V-cycle from zero on level 0:
 // z0 = wj b0 / D (C: level-0 arithmetic type).
@@ -2086,6 +2147,7 @@ struct ApplyArgs {
   const O* r;
   S* p[2];
   RedBuf red;
+  CgTiles N;
 };
 
 template <class O, class S>
@@ -2145,7 +2207,7 @@ __device__ __forceinline__ void apply4_body(const ApplyArgs<O, S>& a, const Tile
   double zr = 0.0, zq = 0.0, zw = 0.0;
   if (valid) {
     const Geom& g = L.g;
-    const int i0 = 4 * (c.tx * MBX + threadIdx.x), j = c.ty * MBY + threadIdx.y;
+    const int i0 = 4 * c.i, j = c.j;
     if (i0 < g.nx && j < g.ny) {
       const bool d3 = g.dim == 3;
       const int k0 = c.tz * a.T.cz, k1 = min(g.nz, k0 + a.T.cz);
@@ -2178,13 +2240,29 @@ __device__ __forceinline__ void apply4_body(const ApplyArgs<O, S>& a, const Tile
     }
   }
   double vv[3] = {zr, zq, zw};
-  block_partial<3, R_SUM, MBS>(vv, red, c.pb);
+  cg_partial<3>(vv, red, c, a.T, a.N, valid);
 }
 NFVM_TILE_KERNELS(k_fcg_apply4, apply4_body, ApplyArgs, (O, S), (class O, class S), (O, S), MBS,
                   true)
 
 // Whether the level-0 CG passes take their four-cells-per-thread kernels.
 __host__ inline bool cg_quad(const Level& l0) { return l0.code && l0.g.nx % 4 == 0; }
+
+// Tiles of a level-0 CG pass (kid: its tile target) and of its partials.
+__host__ inline Tiles cg_tiles(const Level& l0, int kid, CgTiles& N) {
+  const bool quad = cg_quad(l0);
+  const int nq = l0.g.nx / 4;
+  Tiles T = quad ? make_tiles(nq, l0.g.ny, l0.g.nz, l0.tt[kid]) : lvl_tiles(l0, kid);
+  N = CgTiles{T.grid, T.total, T.nty};
+  const int lw = quad_lw(nq);
+  if (quad && lw < 6 && !l0.tiles64) {  // (one 64-wide tile across)
+    T.lw = lw;
+    T.nty = (l0.g.ny + (MBS >> lw) - 1) / (MBS >> lw);
+    T.total = T.nty * T.ntz;
+    T.grid = (T.total + 7) / 8 * 8;
+  }
+  return T;
+}
 
 constexpr int FIN_NV3 = 3;
 
@@ -2233,21 +2311,21 @@ __global__ __launch_bounds__(FIN) void k_fin_apply_batch(Pack<FinArgs> f) {
 
 template <class O, class S>
 ApplyArgs<O, S> apply_args(const Level& l0, const O* r, void* const* dir, const RedBuf& red) {
-  const Tiles T = cg_quad(l0) ? make_tiles(l0.g.nx / 4, l0.g.ny, l0.g.nz, l0.tt[TK_APPLY])
-                              : lvl_tiles(l0, TK_APPLY);
-  return ApplyArgs<O, S>{view(l0), T, (const S*)l0.x[l0.cur], r, {(S*)dir[0], (S*)dir[1]}, red};
+  CgTiles N;
+  const Tiles T = cg_tiles(l0, TK_APPLY, N);
+  return ApplyArgs<O, S>{view(l0), T, (const S*)l0.x[l0.cur], r, {(S*)dir[0], (S*)dir[1]}, red, N};
 }
 
 template <class O, class S>
 void launch_fcg_apply(const Level& l0, const O* r, void* const* dir, const RedBuf& red,
                       hipStream_t s, bool fin) {
   const ApplyArgs<O, S> a = apply_args<O, S>(l0, r, dir, red);
-  check_partials(red, a.T.grid, 3);
+  check_partials(red, a.N.nb, 3);
   if (cg_quad(l0))
     NFVM_LAUNCH((k_fcg_apply4<O, S>), dim3(a.T.grid), dim3(MBX, MBY), 0, s, a);
   else
     NFVM_LAUNCH((k_fcg_apply<O, S>), dim3(a.T.grid), dim3(MBX, MBY), 0, s, a);
-  if (fin) NFVM_LAUNCH_FIN(k_fin_apply, dim3(1), dim3(FIN), 0, s, FinArgs{red, a.T.grid});
+  if (fin) NFVM_LAUNCH_FIN(k_fin_apply, dim3(1), dim3(FIN), 0, s, FinArgs{red, a.N.nb});
 }
 
 // p = z + beta p_prev (stored in S), x += alpha p, r -= alpha A p, ||r||^2,
@@ -2273,6 +2351,7 @@ struct UpdateArgs {
   S* z0;
   S wj;
   RedBuf red;
+  CgTiles N;
 };
 
 template <class O, class S>
@@ -2366,7 +2445,7 @@ __device__ __forceinline__ void update4_body(const UpdateArgs<O, S>& A, const Ti
   };
   if (valid) {
     const Geom& g = L.g;
-    const int i0 = 4 * (c.tx * MBX + threadIdx.x), j = c.ty * MBY + threadIdx.y;
+    const int i0 = 4 * c.i, j = c.j;
     if (i0 < g.nx && j < g.ny) {
       const bool d3 = g.dim == 3;
       const int k0 = c.tz * A.T.cz, k1 = min(g.nz, k0 + A.T.cz);
@@ -2412,7 +2491,7 @@ __device__ __forceinline__ void update4_body(const UpdateArgs<O, S>& A, const Ti
     }
   }
   double vv[1] = {rr};
-  block_partial<1, R_SUM, MBS>(vv, red, c.pb);
+  cg_partial<1>(vv, red, c, A.T, A.N, valid);
 }
 NFVM_TILE_KERNELS(k_fcg_update4, update4_body, UpdateArgs, (O, S), (class O, class S), (O, S),
                   MBS, true)
@@ -2438,22 +2517,22 @@ __global__ __launch_bounds__(FIN) void k_fin_update_batch(Pack<FinArgs> f) {
 template <class O, class S>
 UpdateArgs<O, S> update_args(const Level& l0, O* x, O* r, void* const* dir, const RedBuf& red,
                              void* z0, double wj) {
-  const Tiles T = cg_quad(l0) ? make_tiles(l0.g.nx / 4, l0.g.ny, l0.g.nz, l0.tt[TK_UPDATE])
-                              : lvl_tiles(l0, TK_UPDATE);
+  CgTiles N;
+  const Tiles T = cg_tiles(l0, TK_UPDATE, N);
   return UpdateArgs<O, S>{view(l0), T, x, r, {(S*)dir[0], (S*)dir[1]}, (const S*)l0.x[l0.cur],
-                          (S*)l0.b, (S*)z0, (S)wj, red};
+                          (S*)l0.b, (S*)z0, (S)wj, red, N};
 }
 
 template <class O, class S>
 void launch_fcg_update(const Level& l0, O* x, O* r, void* const* dir, const RedBuf& red,
                        hipStream_t s, bool fin, void* z0, double wj) {
   const UpdateArgs<O, S> a = update_args<O, S>(l0, x, r, dir, red, z0, wj);
-  check_partials(red, a.T.grid, 1);
+  check_partials(red, a.N.nb, 1);
   if (cg_quad(l0))
     NFVM_LAUNCH((k_fcg_update4<O, S>), dim3(a.T.grid), dim3(MBX, MBY), 0, s, a);
   else
     NFVM_LAUNCH((k_fcg_update<O, S>), dim3(a.T.grid), dim3(MBX, MBY), 0, s, a);
-  if (fin) NFVM_LAUNCH_FIN(k_fin_update, dim3(1), dim3(FIN), 0, s, FinArgs{red, a.T.grid});
+  if (fin) NFVM_LAUNCH_FIN(k_fin_update, dim3(1), dim3(FIN), 0, s, FinArgs{red, a.N.nb});
 }
 
 // ---- Algorithm 1's plain iteration: x += z, then r = b - A x --------------------
@@ -2560,11 +2639,10 @@ template void launch_fcg_flush<double, float>(const Level&, double*, void* const
 
 int fcg_max_blocks(const Level& l0) {
   const Tiles ts = lvl_tiles(l0, TK_START);
-  const Tiles ta = cg_quad(l0) ? make_tiles(l0.g.nx / 4, l0.g.ny, l0.g.nz, l0.tt[TK_APPLY])
-                               : lvl_tiles(l0, TK_APPLY);
-  const Tiles tu = cg_quad(l0) ? make_tiles(l0.g.nx / 4, l0.g.ny, l0.g.nz, l0.tt[TK_UPDATE])
-                               : lvl_tiles(l0, TK_UPDATE);
-  return std::max(ts.grid, std::max(ta.grid, tu.grid));
+  CgTiles na, nu;
+  cg_tiles(l0, TK_APPLY, na);
+  cg_tiles(l0, TK_UPDATE, nu);
+  return std::max(ts.grid, std::max(na.nb, nu.nb));
 }
 
 __global__ void k_fill_f64(double* __restrict__ x, int n, double v) {
@@ -3738,17 +3816,17 @@ void plan_fcg_iteration(MgGridDesc* G, int n, BatchOps& o) {
   for (int i = 0; i < n; ++i) {
     MgGridDesc& d = G[i];
     const auto a = apply_args<O, S0>(d.lv[0], (const O*)d.r, d.dir, d.red);
-    check_partials(d.red, a.T.grid, 3);
+    check_partials(d.red, a.N.nb, 3);
     ap[cg_quad(d.lv[0])].push_back(a);
-    fa.push_back(FinArgs{d.red, a.T.grid});
+    fa.push_back(FinArgs{d.red, a.N.nb});
   }
   for (int i = 0; i < n; ++i) {
     MgGridDesc& d = G[i];
     const auto a = update_args<O, S0>(d.lv[0], (O*)d.x, (O*)d.r, d.dir, d.red,
                                       d.zero[0], d.wj);
-    check_partials(d.red, a.T.grid, 1);
+    check_partials(d.red, a.N.nb, 1);
     up[cg_quad(d.lv[0])].push_back(a);
-    fu.push_back(FinArgs{d.red, a.T.grid});
+    fu.push_back(FinArgs{d.red, a.N.nb});
   }
   emit_tiles(o, ap[0], k_fcg_apply<O, S0>, k_fcg_apply_batch<O, S0>, true);
   emit_tiles(o, ap[1], k_fcg_apply4<O, S0>, k_fcg_apply4_batch<O, S0>, true);

@@ -27,10 +27,11 @@ Geom make_geom(int dim, int nx, int ny, int nz, double hx, double hy, double hz)
   return g;
 }
 
-Tiles make_tiles(int nx, int ny, int nz, int target_blocks) {
+Tiles make_tiles(int nx, int ny, int nz, int target_blocks, int lw) {
   Tiles t;
-  t.ntx = (nx + 63) / 64;
-  t.nty = (ny + 3) / 4;
+  t.lw = lw;
+  t.ntx = (nx + (1 << lw) - 1) >> lw;
+  t.nty = (ny + (256 >> lw) - 1) / (256 >> lw);
   const int nxy = t.ntx * t.nty;
   int nzc = (target_blocks + nxy - 1) / nxy;
   if (nzc < 1) nzc = 1;

@@ -103,8 +103,9 @@ Geom make_geom(int dim, int nx, int ny, int nz, double hx, double hy, double hz)
 // tiles (x fastest), so neighbouring tiles mostly share an L2.
 struct Tiles {
   int ntx, nty, ntz, cz, total, grid;
+  int lw;  // log2 of a tile's columns (256 threads: 256 >> lw rows)
 };
-Tiles make_tiles(int nx, int ny, int nz, int target_blocks);
+Tiles make_tiles(int nx, int ny, int nz, int target_blocks, int lw = 6);
 __device__ __forceinline__ bool tile_of(const Tiles& T, int& tx, int& ty, int& tz) {
   const int per = T.grid >> 3;
   const int b = blockIdx.x;
@@ -153,6 +154,7 @@ struct Level {
                                 // as nearest (piecewise constant), not linear
   bool wide = false;            // coarse level stored in the level-0 type (mixed
                                 // precision: FP32 instead of BF16)
+  bool tiles64 = false;         // CG passes on 64 x 4 tiles (while they are tuned)
 };
 
 // Level-0 face code of a cell: 2 bits per face (x-, x+, y-, y+, z-, z+ from
