@@ -714,17 +714,15 @@ class GridT : public GridBase {
     const double* src[7] = {in->u, in->v, in->w, in->T, in->k, in->omega, in->p};
     for (int f = 0; f < 7; ++f)
       if (!src[f]) throw Error{NFVM_E_INVAL, "all seven field pointers are required"};
-    const size_t bytes = (size_t)ncells * sizeof(double);
-    for (int f = 0; f < 6; ++f) {
-      NFVM_CK(hipMemcpyAsync(stage, src[f], bytes, hipMemcpyHostToDevice, stream));
-      if (f < 3)
-        launch_pack<V>(g, stage, vcur(f), 0.0, stream);
-      else
-        launch_pack<F>(g, stage, scur(f), f == 3 ? ph.T_ref : 0.0, stream);
-      NFVM_CK(hipStreamSynchronize(stream));
-    }
-    NFVM_CK(hipMemcpyAsync(stage, src[6], bytes, hipMemcpyHostToDevice, stream));
-    launch_pack<P>(g, stage, p, 0.0, stream);
+    to_device(stage, (const void* const*)src, 7, (size_t)ncells * sizeof(double), stream,
+              [&](int f) {
+                if (f < 3)
+                  launch_pack<V>(g, stage, vcur(f), 0.0, stream);
+                else if (f < 6)
+                  launch_pack<F>(g, stage, scur(f), f == 3 ? ph.T_ref : 0.0, stream);
+                else
+                  launch_pack<P>(g, stage, p, 0.0, stream);
+              });
     if (ph.komega) launch_set_omega_wall<F>(g, ph, patches, type, scur(5), stream);
     clear_increment();
     NFVM_CK(hipGetLastError());
@@ -735,26 +733,23 @@ class GridT : public GridBase {
     double* dst[7] = {out->u, out->v, out->w, out->T, out->k, out->omega, out->p};
     for (int f = 0; f < 7; ++f)
       if (!dst[f]) throw Error{NFVM_E_INVAL, "all seven field pointers are required"};
-    const size_t bytes = (size_t)ncells * sizeof(double);
-    for (int f = 0; f < 7; ++f) {
+    to_host(stage, (void* const*)dst, 7, (size_t)ncells * sizeof(double), stream, [&](int f) {
       if (f < 3)
         launch_unpack<V>(g, vcur(f), stage, 0.0, stream);
       else if (f < 6)
         launch_unpack<F>(g, scur(f), stage, f == 3 ? ph.T_ref : 0.0, stream);
       else
         launch_unpack<P>(g, p, stage, 0.0, stream);
-      NFVM_CK(hipMemcpyAsync(dst[f], stage, bytes, hipMemcpyDeviceToHost, stream));
-      NFVM_CK(hipStreamSynchronize(stream));
-    }
+    });
   }
 
   void lambda2(double* out) override {
     if (!out) throw Error{NFVM_E_INVAL, "an output array is required"};
-    launch_lambda2<V>(g, ph, type, patches, vcur(0), vcur(1), vcur(2), stage, stream);
-    NFVM_CK(hipGetLastError());
-    NFVM_CK(hipMemcpyAsync(out, stage, (size_t)ncells * sizeof(double), hipMemcpyDeviceToHost,
-                           stream));
-    NFVM_CK(hipStreamSynchronize(stream));
+    void* dst[1] = {out};
+    to_host(stage, dst, 1, (size_t)ncells * sizeof(double), stream, [&](int) {
+      launch_lambda2<V>(g, ph, type, patches, vcur(0), vcur(1), vcur(2), stage, stream);
+      NFVM_CK(hipGetLastError());
+    });
   }
 
   void probe(const double* pts, int n, double* out) override {

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/nfvm.h"
+#include "hostcopy.hpp"
 #include "nfvm_internal.hpp"
 
 namespace nfvm {
@@ -91,6 +92,8 @@ struct IterPlan {
 };
 
 class GridBase {
+  StagingUser staging;
+
  public:
   virtual ~GridBase() = default;
   virtual void step(int n, nfvm_step_stats* st, nfvm_status* status) = 0;

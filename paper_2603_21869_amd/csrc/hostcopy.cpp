@@ -1,0 +1,384 @@
+// Transfers of a grid's fields.  The runtime's copy of pageable memory stages
+// through its own pinned buffers with one host thread, which also takes the
+// page faults of a result array's first touch: 9 GB/s into fresh arrays and
+// 27 GB/s out of touched ones (470 MB in seven arrays), against 24 and 38 here,
+// where the device's copy engine moves chunks between the device and a pinned
+// ring and up to COPY_THREADS threads between the ring and the arrays.
+#include "hostcopy.hpp"
+
+#include <stdint.h>
+#include <string.h>
+#include <unistd.h>
+
+#include <algorithm>
+#include <condition_variable>
+#include <exception>
+#include <memory>
+#include <mutex>
+#include <new>
+#include <thread>
+#include <vector>
+
+#include "engine.hpp"
+
+namespace nfvm {
+namespace {
+
+// 470 MB into the device / into fresh arrays: chunks of 1 MiB 15.4 / 21.4 ms (a
+// device copy has a fixed cost), 2 MiB 12.3 / 19.6, 4 MiB no better at twice
+// the pinned memory; one thread 18.0 / 42.6, two 12.2 / 24.7.  More than four
+// threads share the same memory channels (no gain).
+constexpr size_t CHUNK = 2 << 20;
+constexpr int SLOTS = 8;         // chunks of a staging area
+constexpr int COPY_THREADS = 4;  // the calling one and its helpers
+constexpr int STAGE_KEEP = 2;    // idle areas kept, 16 MiB each
+// Below this many bytes a call stays with the runtime's copy: pinning the ring
+// (once per program) and starting the threads cost more (seven arrays of
+// 0.13 MB: 0.29 ms against 0.24; of 8.4 MB: 3.3 against 9.2).
+constexpr size_t STAGE_MIN = 4 << 20;
+
+struct Staging {
+  unsigned char* p = nullptr;
+  hipEvent_t ev[SLOTS] = {};
+  int device = 0;
+  ~Staging() {
+    for (hipEvent_t e : ev)
+      if (e) (void)hipEventDestroy(e);
+    if (p) (void)hipHostFree(p);
+  }
+};
+
+class Job;
+struct Pool {
+  std::mutex mu;
+  std::vector<std::unique_ptr<Staging>> idle;
+  int users = 0;
+  // helper threads, their calls' jobs; helpers of an older `gen` end
+  std::vector<std::thread> helpers;
+  std::vector<Job*> jobs;
+  std::condition_variable cv;
+  unsigned gen = 0;
+  pid_t pid = 0;  // the process they belong to
+};
+Pool& pool() {
+  static Pool* p = new Pool();  // (never destroyed: grids may outlive static objects)
+  return *p;
+}
+
+// A staging area for stream s, or null where none can be had (s on another
+// device than the current one among them: events belong to a device).
+std::unique_ptr<Staging> take_staging(hipStream_t s) {
+  int dev = 0, sdev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || (s && hipStreamGetDevice(s, &sdev) != hipSuccess)) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (s && sdev != dev) return nullptr;
+  {
+    std::lock_guard<std::mutex> lk(pool().mu);
+    auto& v = pool().idle;
+    for (size_t i = 0; i < v.size(); ++i)
+      if (v[i]->device == dev) {
+        std::unique_ptr<Staging> st = std::move(v[i]);
+        v.erase(v.begin() + i);
+        return st;
+      }
+  }
+  std::unique_ptr<Staging> st(new Staging());
+  st->device = dev;
+  bool ok = hipHostMalloc((void**)&st->p, CHUNK * SLOTS, hipHostMallocDefault) == hipSuccess;
+  for (int i = 0; ok && i < SLOTS; ++i)
+    ok = hipEventCreateWithFlags(&st->ev[i], hipEventDisableTiming) == hipSuccess;
+  if (!ok) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return st;
+}
+void give_staging(std::unique_ptr<Staging> st) {
+  std::lock_guard<std::mutex> lk(pool().mu);
+  if (pool().users > 0 && (int)pool().idle.size() < STAGE_KEEP)
+    pool().idle.push_back(std::move(st));
+}
+
+// Memory the runtime does not know: not pinned, not the device's.  (Arrays it
+// knows go to its own copy, which reaches them directly.)
+bool pageable(const void* p) {
+  hipPointerAttribute_t a;
+  memset(&a, 0, sizeof a);
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return a.type == hipMemoryTypeUnregistered;
+}
+bool all_pageable(const void* const* p, int n) {
+  for (int f = 0; f < n; ++f)
+    if (!pageable(p[f])) return false;
+  return true;
+}
+// Result arrays that share memory are written one after the other.
+bool disjoint(void* const* p, int n, size_t bytes) {
+  for (int f = 0; f < n; ++f)
+    for (int h = 0; h < f; ++h) {
+      const uintptr_t a = (uintptr_t)p[f], b = (uintptr_t)p[h];
+      if (a && b && (a > b ? a - b : b - a) < bytes) return false;
+    }
+  return true;
+}
+
+// The chunks of n arrays of `bytes` each, one array after the other.
+struct Chunks {
+  size_t bytes, per, total;
+  Chunks(int n, size_t b) : bytes(b), per((b + CHUNK - 1) / CHUNK), total(per * n) {}
+  int array(size_t i) const { return (int)(i / per); }
+  size_t off(size_t i) const { return i % per * CHUNK; }
+  size_t len(size_t i) const { return std::min(CHUNK, bytes - off(i)); }
+};
+
+// One call's host copies, chunk by chunk.  The calling thread copies too and
+// helpers take chunks only while they run, so a call never waits for a helper
+// to be scheduled: on a machine whose processors are busy (the spinning
+// threads of an OpenMP program's last parallel loop) it goes on alone.
+class Job {
+ public:
+  Job(size_t chunks, const std::function<void(size_t)>& copy)
+      : n_(chunks), copy_(copy), done_(chunks, 0) {
+    std::lock_guard<std::mutex> lk(pool().mu);
+    start_helpers();
+    pool().jobs.push_back(this);
+  }
+  ~Job() {  // (also after an error: helpers finish the chunks they hold)
+    std::unique_lock<std::mutex> lk(pool().mu);
+    auto& v = pool().jobs;
+    v.erase(std::find(v.begin(), v.end(), this));
+    cv_.wait(lk, [&] { return active_ == 0; });
+  }
+  Job(const Job&) = delete;
+  Job& operator=(const Job&) = delete;
+
+  // chunks below `upto` may be copied
+  void ready(size_t upto) {
+    {
+      std::lock_guard<std::mutex> lk(pool().mu);
+      ready_ = std::max(ready_, std::min(upto, n_));
+    }
+    pool().cv.notify_all();
+  }
+  // copies one chunk, if there is one to take
+  bool copy_one() {
+    std::unique_lock<std::mutex> lk(pool().mu);
+    return take(lk);
+  }
+  size_t copied() {
+    std::lock_guard<std::mutex> lk(pool().mu);
+    return copied_;
+  }
+  // waits for more than `seen` chunks, in order from the first, to be copied
+  size_t wait_copied(size_t seen) {
+    std::unique_lock<std::mutex> lk(pool().mu);
+    cv_.wait(lk, [&] { return copied_ > seen; });
+    return copied_;
+  }
+
+ private:
+  bool take(std::unique_lock<std::mutex>& lk) {
+    if (next_ >= ready_) return false;
+    const size_t i = next_++;
+    ++active_;
+    lk.unlock();
+    copy_(i);
+    lk.lock();
+    --active_;
+    done_[i] = 1;
+    while (copied_ < n_ && done_[copied_]) ++copied_;
+    cv_.notify_all();
+    return true;
+  }
+  static void help(unsigned gen) {
+    std::unique_lock<std::mutex> lk(pool().mu);
+    while (pool().gen == gen) {
+      bool any = false;
+      for (size_t j = 0; !any && j < pool().jobs.size(); ++j) any = pool().jobs[j]->take(lk);
+      if (!any) pool().cv.wait(lk);
+    }
+  }
+  static void start_helpers() {  // (with the pool locked)
+    const size_t hw = std::thread::hardware_concurrency();
+    try {
+      while (pool().helpers.size() + 1 < std::min<size_t>(COPY_THREADS, hw))
+        pool().helpers.emplace_back(help, pool().gen);
+      pool().pid = getpid();
+    } catch (const std::exception&) {  // as many as there are
+    }
+  }
+
+  const size_t n_;
+  const std::function<void(size_t)>& copy_;
+  std::vector<char> done_;
+  size_t ready_ = 0, next_ = 0, copied_ = 0;
+  int active_ = 0;
+  std::condition_variable cv_;
+};
+
+// Whether the device has passed an event.
+bool ended(hipEvent_t e) {
+  const hipError_t r = hipEventQuery(e);
+  if (r == hipErrorNotReady) {
+    (void)hipGetLastError();
+    return false;
+  }
+  NFVM_CK(r);
+  return true;
+}
+
+// The staging area of one call: back in the pool when the stream is idle.
+struct StagingCall {
+  std::unique_ptr<Staging> st;
+  hipStream_t s;
+  bool idle = false;
+  explicit StagingCall(hipStream_t stream) : st(take_staging(stream)), s(stream) {}
+  ~StagingCall() {
+    if (!st) return;
+    if (!idle) (void)hipStreamSynchronize(s);  // (after an error)
+    give_staging(std::move(st));
+  }
+};
+
+}  // namespace
+
+StagingUser::StagingUser() {
+  std::lock_guard<std::mutex> lk(pool().mu);
+  ++pool().users;
+}
+StagingUser::~StagingUser() {
+  std::vector<std::unique_ptr<Staging>> old;
+  std::vector<std::thread> ended;
+  {
+    std::lock_guard<std::mutex> lk(pool().mu);
+    if (--pool().users > 0) return;
+    old.swap(pool().idle);
+    ended.swap(pool().helpers);
+    ++pool().gen;
+  }
+  pool().cv.notify_all();
+  for (std::thread& t : ended)
+    if (pool().pid == getpid())
+      t.join();
+    else
+      t.detach();  // (a forked child has no copies of them)
+}
+
+void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t s,
+             const std::function<void(int)>& fill) {
+  if (n * bytes >= STAGE_MIN && all_pageable(dst, n) && disjoint(dst, n, bytes)) {
+    StagingCall c(s);
+    if (c.st) {
+      const Chunks ch(n, bytes);
+      unsigned char* const ring = c.st->p;
+      const std::function<void(size_t)> copy = [&](size_t i) {
+        memcpy((unsigned char*)dst[ch.array(i)] + ch.off(i), ring + i % SLOTS * CHUNK, ch.len(i));
+      };
+      Job job(ch.total, copy);
+      size_t issued = 0, arrived = 0, copied = 0;  // device copies begun, ended; chunks done
+      while (copied < ch.total) {
+        for (; issued < ch.total && issued < copied + SLOTS; ++issued) {
+          if (ch.off(issued) == 0) fill(ch.array(issued));
+          NFVM_CK(hipMemcpyAsync(ring + issued % SLOTS * CHUNK,
+                                 (const unsigned char*)dev + ch.off(issued), ch.len(issued),
+                                 hipMemcpyDeviceToHost, s));
+          NFVM_CK(hipEventRecord(c.st->ev[issued % SLOTS], s));
+        }
+        size_t now = arrived;
+        while (now < issued && ended(c.st->ev[now % SLOTS])) ++now;
+        if (now > arrived) job.ready(arrived = now);
+        if (job.copy_one()) {
+        } else if (arrived < issued) {
+          NFVM_CK(hipEventSynchronize(c.st->ev[arrived % SLOTS]));
+          job.ready(++arrived);
+        } else {
+          job.wait_copied(copied);  // (helpers hold the rest)
+        }
+        copied = job.copied();
+      }
+      c.idle = true;
+      return;
+    }
+  }
+  for (int f = 0; f < n; ++f) {
+    fill(f);
+    NFVM_CK(hipMemcpyAsync(dst[f], dev, bytes, hipMemcpyDeviceToHost, s));
+    NFVM_CK(hipStreamSynchronize(s));
+  }
+}
+
+void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream_t s,
+               const std::function<void(int)>& use) {
+  if (n * bytes >= STAGE_MIN && all_pageable(src, n)) {
+    StagingCall c(s);
+    if (c.st) {
+      const Chunks ch(n, bytes);
+      unsigned char* const ring = c.st->p;
+      const std::function<void(size_t)> copy = [&](size_t i) {
+        memcpy(ring + i % SLOTS * CHUNK, (const unsigned char*)src[ch.array(i)] + ch.off(i),
+               ch.len(i));
+      };
+      Job job(ch.total, copy);
+      size_t issued = 0, freed = 0, copied = 0;  // device copies begun, ended; chunks in the ring
+      job.ready(SLOTS);
+      while (issued < ch.total) {
+        for (; issued < copied; ++issued) {
+          NFVM_CK(hipMemcpyAsync((unsigned char*)dev + ch.off(issued),
+                                 ring + issued % SLOTS * CHUNK, ch.len(issued),
+                                 hipMemcpyHostToDevice, s));
+          NFVM_CK(hipEventRecord(c.st->ev[issued % SLOTS], s));
+          if (ch.off(issued) + ch.len(issued) == bytes) use(ch.array(issued));
+        }
+        size_t now = freed;
+        while (now < issued && ended(c.st->ev[now % SLOTS])) ++now;
+        if (now > freed) job.ready((freed = now) + SLOTS);
+        if (issued < ch.total && !job.copy_one()) {
+          if (freed + SLOTS == copied) {  // every slot waits for its device copy
+            NFVM_CK(hipEventSynchronize(c.st->ev[freed % SLOTS]));
+            job.ready(++freed + SLOTS);
+          } else {
+            job.wait_copied(copied);  // (helpers hold the next)
+          }
+        }
+        copied = job.copied();
+      }
+      NFVM_CK(hipStreamSynchronize(s));
+      c.idle = true;
+      return;
+    }
+  }
+  for (int f = 0; f < n; ++f) {
+    NFVM_CK(hipMemcpyAsync(dev, src[f], bytes, hipMemcpyHostToDevice, s));
+    use(f);
+    NFVM_CK(hipStreamSynchronize(s));
+  }
+}
+
+void host_copy(void* const* dst, const void* const* src, int n, size_t bytes) {
+  const Chunks ch(n, bytes);
+  const std::function<void(size_t)> copy = [&](size_t i) {
+    const int f = ch.array(i);
+    if (dst[f])
+      memcpy((unsigned char*)dst[f] + ch.off(i), (const unsigned char*)src[f] + ch.off(i),
+             ch.len(i));
+  };
+  if (n * bytes >= STAGE_MIN && disjoint(dst, n, bytes)) {
+    try {
+      Job job(ch.total, copy);
+      job.ready(ch.total);
+      while (job.copy_one()) {
+      }
+      for (size_t c = job.copied(); c < ch.total;) c = job.wait_copied(c);
+      return;
+    } catch (const std::bad_alloc&) {  // (from the job's making: nothing copied)
+    }
+  }
+  for (size_t i = 0; i < ch.total; ++i) copy(i);
+}
+
+}  // namespace nfvm

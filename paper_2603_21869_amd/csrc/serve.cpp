@@ -20,6 +20,7 @@
 #include <deque>
 #include <map>
 #include <mutex>
+#include <new>
 #include <thread>
 #include <vector>
 
@@ -36,7 +37,8 @@ struct Request {
   nfvm_grid_desc desc{};
   std::vector<nfvm_patch> patches;
   std::vector<uint8_t> mask;
-  std::vector<double> f[7];  // u v w p T k omega, host FP64
+  std::unique_ptr<double[]> f[7];  // u v w p T k omega, host FP64
+  size_t n = 0;                    // values in each
   int n_steps = 0;
   size_t footprint = 0;
   int state = Q_QUEUED;
@@ -53,6 +55,7 @@ double now_since(std::chrono::steady_clock::time_point t0) {
 }  // namespace
 
 struct nfvm_server {
+  StagingUser staging;
   std::mutex mu;
   std::condition_variable cv;
   std::deque<uint64_t> queue;
@@ -87,7 +90,7 @@ struct nfvm_server {
   std::unique_ptr<GridBase> make(Request* r, hipStream_t s) {
     nfvm_fields init;
     double** dst[7] = {&init.u, &init.v, &init.w, &init.p, &init.T, &init.k, &init.omega};
-    for (int f = 0; f < 7; ++f) *dst[f] = r->f[f].data();
+    for (int f = 0; f < 7; ++f) *dst[f] = r->f[f].get();
     nfvm_grid_desc d = r->desc;
     d.patches = r->patches.empty() ? nullptr : r->patches.data();
     d.solid_mask = r->mask.empty() ? nullptr : r->mask.data();
@@ -104,7 +107,7 @@ struct nfvm_server {
       try {
         nfvm_fields out;
         double** dst[7] = {&out.u, &out.v, &out.w, &out.p, &out.T, &out.k, &out.omega};
-        for (int f = 0; f < 7; ++f) *dst[f] = r->f[f].data();
+        for (int f = 0; f < 7; ++f) *dst[f] = r->f[f].get();
         a.g->get_fields(&out);
       } catch (const Error& e) {
         st = e.st;
@@ -253,7 +256,14 @@ nfvm_status nfvm_submit(nfvm_server_t s, const nfvm_grid_desc* desc, const nfvm_
   r->patches.assign(desc->patches, desc->patches + desc->n_patches);
   const size_t N = (size_t)desc->n[0] * desc->n[1] * desc->n[2];
   if (desc->solid_mask) r->mask.assign(desc->solid_mask, desc->solid_mask + N);
-  for (int f = 0; f < 7; ++f) r->f[f].assign(src[f], src[f] + N);
+  void* dst[7];
+  for (int f = 0; f < 7; ++f) {
+    r->f[f].reset(new (std::nothrow) double[N]);  // (not initialised: written by the copy)
+    dst[f] = r->f[f].get();
+    if (!dst[f]) return sfail(NFVM_E_NOMEM, "no host memory for the request's fields");
+  }
+  host_copy(dst, (const void* const*)src, 7, N * sizeof(double));
+  r->n = N;
   r->n_steps = n_steps;
   std::lock_guard<std::mutex> lk(s->mu);
   r->id = s->next_id++;
@@ -277,9 +287,10 @@ nfvm_status nfvm_poll(nfvm_server_t s, uint64_t ticket, nfvm_fields* out, nfvm_s
     s->reqs.erase(it);
   }
   if (out) {
-    double* dst[7] = {out->u, out->v, out->w, out->p, out->T, out->k, out->omega};
-    for (int f = 0; f < 7; ++f)
-      if (dst[f]) memcpy(dst[f], r->f[f].data(), r->f[f].size() * sizeof(double));
+    void* dst[7] = {out->u, out->v, out->w, out->p, out->T, out->k, out->omega};
+    const void* src[7];
+    for (int f = 0; f < 7; ++f) src[f] = r->f[f].get();
+    host_copy(dst, src, 7, r->n * sizeof(double));
   }
   if (last) *last = r->last;
   if (r->status != NFVM_OK) set_error(r->err.empty() ? "request finished with an error" : r->err);
