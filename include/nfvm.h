@@ -482,16 +482,17 @@ nfvm_status nfvm_profile_read(nfvm_grid_t grid, int32_t kernel, int64_t* launche
  *                     alone: nfvm_step_batch refuses them (NFVM_E_INVAL).
  *                     Other values: NFVM_E_INVAL.
  *   NFVM_OPT_SWEEP_PAIRS  1 (default): consecutive damped-Jacobi sweeps on
- *                     the finest level run two per pass (x, b and the face
- *                     codes read once for both) where its rows are a
- *                     multiple of 4 cells, as many as keep the V-cycle's
- *                     result out of the buffer the next cycle's first sweep
- *                     is fused into; the fields are bitwise those of single
- *                     sweeps.  On small grids (131072 cells) up to three
- *                     run in one pass, with the transfer next to them, in
- *                     batched iterations (nfvm_step_batch, serving) too;
- *                     on larger ones those take single sweeps.  0: one
- *                     sweep per pass.
+ *                     the finest level run several per pass where that is
+ *                     the faster form; the fields are bitwise those of
+ *                     single sweeps.  On small grids (131072 cells) up to
+ *                     three run in one pass, with the transfer next to
+ *                     them, in batched iterations (nfvm_step_batch, serving)
+ *                     too.  On grids of more than 16777216 cells whose rows
+ *                     are a multiple of 4 cells two run per pass (x, b and
+ *                     the face codes read once for both), as many as keep
+ *                     the V-cycle's result out of the buffer the next
+ *                     cycle's first sweep is fused into.  0: one sweep per
+ *                     pass.
  *                     Other values: NFVM_E_INVAL.
  * Errors: NFVM_E_INVAL for an unknown option. */
 enum {

@@ -879,8 +879,17 @@ __device__ __forceinline__ void smooth2_body(const SmoothArgs<S, C>& a, const Ti
 NFVM_TILE_KERNELS(k_smooth2_code4, smooth2_body, SmoothArgs, (S, C), (class S, class C),
                   (S, C), MBS, false)
 
-// Whether level l takes two-sweep passes (level 0 with four-cell rows).
-bool sweep_pair(const Level& l) { return l.code && l.g.nx % 4 == 0; }
+// Whether level l takes two-sweep passes: level 0 with four-cell rows, of
+// more than PAIR_CELLS cells.  A pass saves HBM bytes and pays in halo lanes,
+// barriers and a longer walk; where x, b and the face codes stay in the 256 MB
+// last-level cache between two sweeps it saves nothing.  Measured per
+// iteration, three sweeps on each side, single / pairs: 2.1M cells (256 x 128 x
+// 64) mixed 208 / 242 us, FP64 273 / 313; 8.4M 492 / 561, 782 / 867; 16.8M
+// 855 / 896, 1396 / 1428; 33.6M 1594 / 1507, 2505 / 2434.
+constexpr long long PAIR_CELLS = 1 << 24;
+bool sweep_pair(const Level& l) {
+  return l.code && l.g.nx % 4 == 0 && l.g.cells() > PAIR_CELLS;
+}
 
 template <class S, class C>
 void launch_smooth2(const Level& l, const void* xin, void* xout, double wj, const double* ctl,
