@@ -221,6 +221,15 @@ class Job {
   std::condition_variable cv_;
 };
 
+// fn(f), which launches kernels: a launch that fails leaves its code as the
+// thread's last error, which is taken here, before an event query that is not
+// ready overwrites it.  (An error from before the call is not the call's.)
+void launched(const std::function<void(int)>& fn, int f) {
+  const bool clean = hipPeekAtLastError() == hipSuccess;
+  fn(f);
+  if (clean) NFVM_CK(hipGetLastError());
+}
+
 // Whether the device has passed an event.
 bool ended(hipEvent_t e) {
   const hipError_t r = hipEventQuery(e);
@@ -283,7 +292,7 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
       size_t issued = 0, arrived = 0, copied = 0;  // device copies begun, ended; chunks done
       while (copied < ch.total) {
         for (; issued < ch.total && issued < copied + SLOTS; ++issued) {
-          if (ch.off(issued) == 0) fill(ch.array(issued));
+          if (ch.off(issued) == 0) launched(fill, ch.array(issued));
           NFVM_CK(hipMemcpyAsync(ring + issued % SLOTS * CHUNK,
                                  (const unsigned char*)dev + ch.off(issued), ch.len(issued),
                                  hipMemcpyDeviceToHost, s));
@@ -306,7 +315,7 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
     }
   }
   for (int f = 0; f < n; ++f) {
-    fill(f);
+    launched(fill, f);
     NFVM_CK(hipMemcpyAsync(dst[f], dev, bytes, hipMemcpyDeviceToHost, s));
     NFVM_CK(hipStreamSynchronize(s));
   }
@@ -332,7 +341,7 @@ void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream
                                  ring + issued % SLOTS * CHUNK, ch.len(issued),
                                  hipMemcpyHostToDevice, s));
           NFVM_CK(hipEventRecord(c.st->ev[issued % SLOTS], s));
-          if (ch.off(issued) + ch.len(issued) == bytes) use(ch.array(issued));
+          if (ch.off(issued) + ch.len(issued) == bytes) launched(use, ch.array(issued));
         }
         size_t now = freed;
         while (now < issued && ended(c.st->ev[now % SLOTS])) ++now;
@@ -354,7 +363,7 @@ void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream
   }
   for (int f = 0; f < n; ++f) {
     NFVM_CK(hipMemcpyAsync(dev, src[f], bytes, hipMemcpyHostToDevice, s));
-    use(f);
+    launched(use, f);
     NFVM_CK(hipStreamSynchronize(s));
   }
 }
