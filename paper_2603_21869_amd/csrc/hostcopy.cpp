@@ -51,7 +51,7 @@ struct Staging {
 class Job;
 struct Pool {
   std::mutex mu;
-  std::vector<std::unique_ptr<Staging>> idle;
+  std::unique_ptr<Staging> idle[STAGE_KEEP];
   int users = 0;
   // helper threads, their calls' jobs; helpers of an older `gen` end
   std::vector<std::thread> helpers;
@@ -76,15 +76,11 @@ std::unique_ptr<Staging> take_staging(hipStream_t s) {
   if (s && sdev != dev) return nullptr;
   {
     std::lock_guard<std::mutex> lk(pool().mu);
-    auto& v = pool().idle;
-    for (size_t i = 0; i < v.size(); ++i)
-      if (v[i]->device == dev) {
-        std::unique_ptr<Staging> st = std::move(v[i]);
-        v.erase(v.begin() + i);
-        return st;
-      }
+    for (std::unique_ptr<Staging>& st : pool().idle)
+      if (st && st->device == dev) return std::move(st);
   }
-  std::unique_ptr<Staging> st(new Staging());
+  std::unique_ptr<Staging> st(new (std::nothrow) Staging());
+  if (!st) return nullptr;
   st->device = dev;
   bool ok = hipHostMalloc((void**)&st->p, CHUNK * SLOTS, hipHostMallocDefault) == hipSuccess;
   for (int i = 0; ok && i < SLOTS; ++i)
@@ -97,8 +93,12 @@ std::unique_ptr<Staging> take_staging(hipStream_t s) {
 }
 void give_staging(std::unique_ptr<Staging> st) {
   std::lock_guard<std::mutex> lk(pool().mu);
-  if (pool().users > 0 && (int)pool().idle.size() < STAGE_KEEP)
-    pool().idle.push_back(std::move(st));
+  if (pool().users == 0) return;
+  for (std::unique_ptr<Staging>& slot : pool().idle)
+    if (!slot) {
+      slot = std::move(st);
+      return;
+    }
 }
 
 // Memory the runtime does not know: not pinned, not the device's.  (Arrays it
@@ -136,13 +136,27 @@ struct Chunks {
   size_t len(size_t i) const { return std::min(CHUNK, bytes - off(i)); }
 };
 
+// A reference to a function of a chunk's index (a std::function of more than
+// two captures would allocate).
+class ChunkCopy {
+ public:
+  template <class F>
+  explicit ChunkCopy(const F& f)
+      : call_([](const void* p, size_t i) { (*(const F*)p)(i); }), f_(&f) {}
+  void operator()(size_t i) const { call_(f_, i); }
+
+ private:
+  void (*call_)(const void*, size_t);
+  const void* f_;
+};
+
 // One call's host copies, chunk by chunk.  The calling thread copies too and
 // helpers take chunks only while they run, so a call never waits for a helper
 // to be scheduled: on a machine whose processors are busy (the spinning
 // threads of an OpenMP program's last parallel loop) it goes on alone.
 class Job {
  public:
-  Job(size_t chunks, const std::function<void(size_t)>& copy)
+  Job(size_t chunks, const ChunkCopy& copy)
       : n_(chunks), copy_(copy), done_(chunks, 0) {
     std::lock_guard<std::mutex> lk(pool().mu);
     start_helpers();
@@ -214,12 +228,21 @@ class Job {
   }
 
   const size_t n_;
-  const std::function<void(size_t)>& copy_;
+  const ChunkCopy copy_;
   std::vector<char> done_;
   size_t ready_ = 0, next_ = 0, copied_ = 0;
   int active_ = 0;
   std::condition_variable cv_;
 };
+
+// Null where there is no host memory for it.
+std::unique_ptr<Job> make_job(size_t chunks, const ChunkCopy& copy) {
+  try {
+    return std::unique_ptr<Job>(new Job(chunks, copy));
+  } catch (const std::bad_alloc&) {
+    return nullptr;
+  }
+}
 
 // fn(f), which launches kernels: a launch that fails leaves its code as the
 // thread's last error, which is taken here, before an event query that is not
@@ -261,12 +284,12 @@ StagingUser::StagingUser() {
   ++pool().users;
 }
 StagingUser::~StagingUser() {
-  std::vector<std::unique_ptr<Staging>> old;
+  std::unique_ptr<Staging> old[STAGE_KEEP];
   std::vector<std::thread> ended;
   {
     std::lock_guard<std::mutex> lk(pool().mu);
     if (--pool().users > 0) return;
-    old.swap(pool().idle);
+    std::swap(old, pool().idle);
     ended.swap(pool().helpers);
     ++pool().gen;
   }
@@ -282,13 +305,12 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
              const std::function<void(int)>& fill) {
   if (n * bytes >= STAGE_MIN && all_pageable(dst, n) && disjoint(dst, n, bytes)) {
     StagingCall c(s);
-    if (c.st) {
-      const Chunks ch(n, bytes);
-      unsigned char* const ring = c.st->p;
-      const std::function<void(size_t)> copy = [&](size_t i) {
-        memcpy((unsigned char*)dst[ch.array(i)] + ch.off(i), ring + i % SLOTS * CHUNK, ch.len(i));
-      };
-      Job job(ch.total, copy);
+    const Chunks ch(n, bytes);
+    unsigned char* const ring = c.st ? c.st->p : nullptr;
+    const auto copy = [&](size_t i) {
+      memcpy((unsigned char*)dst[ch.array(i)] + ch.off(i), ring + i % SLOTS * CHUNK, ch.len(i));
+    };
+    if (const std::unique_ptr<Job> job = ring ? make_job(ch.total, ChunkCopy(copy)) : nullptr) {
       size_t issued = 0, arrived = 0, copied = 0;  // device copies begun, ended; chunks done
       while (copied < ch.total) {
         for (; issued < ch.total && issued < copied + SLOTS; ++issued) {
@@ -300,15 +322,15 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
         }
         size_t now = arrived;
         while (now < issued && ended(c.st->ev[now % SLOTS])) ++now;
-        if (now > arrived) job.ready(arrived = now);
-        if (job.copy_one()) {
+        if (now > arrived) job->ready(arrived = now);
+        if (job->copy_one()) {
         } else if (arrived < issued) {
           NFVM_CK(hipEventSynchronize(c.st->ev[arrived % SLOTS]));
-          job.ready(++arrived);
+          job->ready(++arrived);
         } else {
-          job.wait_copied(copied);  // (helpers hold the rest)
+          job->wait_copied(copied);  // (helpers hold the rest)
         }
-        copied = job.copied();
+        copied = job->copied();
       }
       c.idle = true;
       return;
@@ -325,16 +347,15 @@ void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream
                const std::function<void(int)>& use) {
   if (n * bytes >= STAGE_MIN && all_pageable(src, n)) {
     StagingCall c(s);
-    if (c.st) {
-      const Chunks ch(n, bytes);
-      unsigned char* const ring = c.st->p;
-      const std::function<void(size_t)> copy = [&](size_t i) {
-        memcpy(ring + i % SLOTS * CHUNK, (const unsigned char*)src[ch.array(i)] + ch.off(i),
-               ch.len(i));
-      };
-      Job job(ch.total, copy);
+    const Chunks ch(n, bytes);
+    unsigned char* const ring = c.st ? c.st->p : nullptr;
+    const auto copy = [&](size_t i) {
+      memcpy(ring + i % SLOTS * CHUNK, (const unsigned char*)src[ch.array(i)] + ch.off(i),
+             ch.len(i));
+    };
+    if (const std::unique_ptr<Job> job = ring ? make_job(ch.total, ChunkCopy(copy)) : nullptr) {
       size_t issued = 0, freed = 0, copied = 0;  // device copies begun, ended; chunks in the ring
-      job.ready(SLOTS);
+      job->ready(SLOTS);
       while (issued < ch.total) {
         for (; issued < copied; ++issued) {
           NFVM_CK(hipMemcpyAsync((unsigned char*)dev + ch.off(issued),
@@ -345,16 +366,16 @@ void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream
         }
         size_t now = freed;
         while (now < issued && ended(c.st->ev[now % SLOTS])) ++now;
-        if (now > freed) job.ready((freed = now) + SLOTS);
-        if (issued < ch.total && !job.copy_one()) {
+        if (now > freed) job->ready((freed = now) + SLOTS);
+        if (issued < ch.total && !job->copy_one()) {
           if (freed + SLOTS == copied) {  // every slot waits for its device copy
             NFVM_CK(hipEventSynchronize(c.st->ev[freed % SLOTS]));
-            job.ready(++freed + SLOTS);
+            job->ready(++freed + SLOTS);
           } else {
-            job.wait_copied(copied);  // (helpers hold the next)
+            job->wait_copied(copied);  // (helpers hold the next)
           }
         }
-        copied = job.copied();
+        copied = job->copied();
       }
       NFVM_CK(hipStreamSynchronize(s));
       c.idle = true;
@@ -370,21 +391,19 @@ void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream
 
 void host_copy(void* const* dst, const void* const* src, int n, size_t bytes) {
   const Chunks ch(n, bytes);
-  const std::function<void(size_t)> copy = [&](size_t i) {
+  const auto copy = [&](size_t i) {
     const int f = ch.array(i);
     if (dst[f])
       memcpy((unsigned char*)dst[f] + ch.off(i), (const unsigned char*)src[f] + ch.off(i),
              ch.len(i));
   };
   if (n * bytes >= STAGE_MIN && disjoint(dst, n, bytes)) {
-    try {
-      Job job(ch.total, copy);
-      job.ready(ch.total);
-      while (job.copy_one()) {
+    if (const std::unique_ptr<Job> job = make_job(ch.total, ChunkCopy(copy))) {
+      job->ready(ch.total);
+      while (job->copy_one()) {
       }
-      for (size_t c = job.copied(); c < ch.total;) c = job.wait_copied(c);
+      for (size_t c = job->copied(); c < ch.total;) c = job->wait_copied(c);
       return;
-    } catch (const std::bad_alloc&) {  // (from the job's making: nothing copied)
     }
   }
   for (size_t i = 0; i < ch.total; ++i) copy(i);

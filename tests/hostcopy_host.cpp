@@ -1,7 +1,8 @@
 // The field transfers (csrc/hostcopy.cpp) on the CPU: a runtime whose streams
 // run each call at once, whose event queries say "not ready" the first time,
 // and whose last error behaves as HIP's (kept until read, overwritten by a
-// query that is not ready).  Usage: hostcopy_host CASE; ends with 0 if the case
+// query that is not ready); allocations of the calling thread can be made to
+// fail.  Usage: hostcopy_host CASE; ends with 0 if the case
 // holds, with a message and 1 if not.
 #include "../paper_2603_21869_amd/csrc/hostcopy.cpp"
 
@@ -18,7 +19,29 @@ hipError_t set(hipError_t e) {
   if (e != hipSuccess) last = e;
   return e;
 }
+// the allocation of this thread that fails: 0 the next one (-1: none)
+thread_local long deny = -1;
+thread_local bool denied = false;
 }  // namespace fake
+
+void* operator new(size_t n) {
+  if (fake::deny >= 0 && fake::deny-- == 0) {
+    fake::denied = true;
+    throw std::bad_alloc();
+  }
+  void* p = malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void* operator new(size_t n, const std::nothrow_t&) noexcept {
+  try {
+    return operator new(n);
+  } catch (const std::bad_alloc&) {
+    return nullptr;
+  }
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
 
 extern "C" {
 hipError_t hipGetLastError() {
@@ -156,10 +179,68 @@ int launch_error() {
   }
   return 0;
 }
+
+// A transfer that finds no host memory for its own bookkeeping does without:
+// it neither fails nor throws (it runs inside C entry points and, for a served
+// request, at the end of a worker's round), whichever allocation fails.
+template <class F>
+int each_allocation(F&& f) {
+  for (int n = 0; n < 1000; ++n) {
+    StagingUser user;  // (the ring and the threads are made anew)
+    fake::denied = false;
+    if (!f(n)) return fail("a copy without memory");
+    if (!fake::denied) return 0;
+  }
+  return fail("the allocations never ended");
+}
+template <class F>
+bool denying(int n, F&& f) {
+  bool ok = true;
+  fake::deny = n;
+  try {
+    f();
+  } catch (const std::exception&) {
+    ok = false;
+  }
+  fake::deny = -1;
+  return ok;
+}
+
+int no_memory() {
+  const size_t count = 300001, bytes = count * sizeof(double);
+  int rc = each_allocation([&](int n) {
+    Seven g(count, false);
+    const std::function<void(int)> fill = [&g](int f) {
+      for (size_t i = 0; i < g.h.count; ++i) g.dev[i] = Arrays::value(f, i);
+    };
+    return denying(n, [&] { to_host(g.dev.data(), g.p.data(), 7, bytes, nullptr, fill); }) &&
+           g.h.right();
+  });
+  if (rc) return rc;
+  rc = each_allocation([&](int n) {
+    Seven s(count, true);
+    bool ok = true;
+    struct {
+      Seven& s;
+      bool& ok;
+    } c{s, ok};
+    const std::function<void(int)> use = [&c](int f) {
+      for (size_t i = 0; i < c.s.h.count; ++i) c.ok = c.ok && c.s.dev[i] == Arrays::value(f, i);
+    };
+    return denying(n, [&] { to_device(s.dev.data(), s.p.data(), 7, bytes, nullptr, use); }) && ok;
+  });
+  if (rc) return rc;
+  return each_allocation([&](int n) {
+    Arrays a(7, count, true), b(7, count, false);
+    const auto pa = a.ptrs(), pb = b.ptrs();
+    return denying(n, [&] { host_copy(pb.data(), pa.data(), 7, bytes); }) && b.right();
+  });
+}
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string c = argc > 1 ? argv[1] : "";
   if (c == "launch_error") return launch_error();
+  if (c == "no_memory") return no_memory();
   return fail("unknown case");
 }
