@@ -6,9 +6,9 @@
 // ring and up to COPY_THREADS threads between the ring and the arrays.
 #include "hostcopy.hpp"
 
+#include <pthread.h>
 #include <stdint.h>
 #include <string.h>
-#include <unistd.h>
 
 #include <algorithm>
 #include <condition_variable>
@@ -58,11 +58,24 @@ struct Pool {
   std::vector<Job*> jobs;
   std::condition_variable cv;
   unsigned gen = 0;
-  pid_t pid = 0;  // the process they belong to
 };
-Pool& pool() {
-  static Pool* p = new Pool();  // (never destroyed: grids may outlive static objects)
-  return *p;
+void pool_in_child();
+Pool*& pool_of_process() {
+  static Pool* p = [] {
+    (void)pthread_atfork(nullptr, nullptr, pool_in_child);
+    return new Pool();  // (never destroyed: grids may outlive static objects)
+  }();
+  return p;
+}
+Pool& pool() { return *pool_of_process(); }
+// A forked child has its parent's users but none of its threads: it goes on
+// with a pool of its own, as the parent's may be locked and its condition
+// variable counts waiters that the child does not have.
+void pool_in_child() {
+  Pool* p = new (std::nothrow) Pool();
+  if (!p) return;
+  p->users = pool().users;
+  pool_of_process() = p;
 }
 
 // A staging area for stream s, or null where none can be had (s on another
@@ -222,7 +235,6 @@ class Job {
     try {
       while (pool().helpers.size() + 1 < std::min<size_t>(COPY_THREADS, hw))
         pool().helpers.emplace_back(help, pool().gen);
-      pool().pid = getpid();
     } catch (const std::exception&) {  // as many as there are
     }
   }
@@ -294,11 +306,7 @@ StagingUser::~StagingUser() {
     ++pool().gen;
   }
   pool().cv.notify_all();
-  for (std::thread& t : ended)
-    if (pool().pid == getpid())
-      t.join();
-    else
-      t.detach();  // (a forked child has no copies of them)
+  for (std::thread& t : ended) t.join();
 }
 
 void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t s,

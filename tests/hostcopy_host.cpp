@@ -8,6 +8,8 @@
 
 #include <stdio.h>
 #include <stdlib.h>
+#include <sys/wait.h>
+#include <unistd.h>
 
 namespace fake {
 thread_local hipError_t last = hipSuccess;
@@ -236,11 +238,38 @@ int no_memory() {
     return denying(n, [&] { host_copy(pb.data(), pa.data(), 7, bytes); }) && b.right();
   });
 }
+
+// A forked child has none of its parent's helper threads: transfers there work,
+// and so does the end of the last user (which must not wait for them).
+int forked_child() {
+  StagingUser* user = new StagingUser();
+  Seven g(300001, false);
+  g.get();
+  usleep(200000);  // (the helpers are idle)
+  const pid_t pid = fork();
+  if (pid == 0) {
+    alarm(20);
+    Seven c(300001, false);
+    c.get();
+    const bool ok = c.h.right();
+    delete user;
+    StagingUser next;
+    Seven d(300001, false);
+    d.get();
+    _exit(ok && d.h.right() ? 0 : 1);
+  }
+  int st = 0;
+  if (pid < 0 || waitpid(pid, &st, 0) != pid) return fail("fork");
+  delete user;
+  if (!WIFEXITED(st)) return fail("the child did not end by itself");
+  return WEXITSTATUS(st) ? fail("the child's fields") : 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string c = argc > 1 ? argv[1] : "";
   if (c == "launch_error") return launch_error();
   if (c == "no_memory") return no_memory();
+  if (c == "forked_child") return forked_child();
   return fail("unknown case");
 }
