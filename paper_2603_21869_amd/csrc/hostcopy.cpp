@@ -32,10 +32,16 @@ constexpr size_t CHUNK = 2 << 20;
 constexpr int SLOTS = 8;         // chunks of a staging area
 constexpr int COPY_THREADS = 4;  // the calling one and its helpers
 constexpr int STAGE_KEEP = 2;    // idle areas kept, 16 MiB each
-// Below this many bytes a call stays with the runtime's copy: pinning the ring
-// (once per program) and starting the threads cost more (seven arrays of
-// 0.13 MB: 0.29 ms against 0.24; of 8.4 MB: 3.3 against 9.2).
+// Below this many bytes a call stays with the runtime's copy (seven arrays of
+// 0.13 MB: 0.29 ms with the ring, 0.24 without; of 8.4 MB: 3.3 against 9.2).
 constexpr size_t STAGE_MIN = 4 << 20;
+// An area and the helper threads cost 0.2 ms to make and end, for every grid of
+// a program that has one grid at a time (they end with the last).  Without an
+// idle area, a call of fewer than STAGE_COLD bytes makes one only once such
+// calls have moved STAGE_WARM bytes.  Made, read and freed, a mixed-precision
+// grid with the ring / without: 48^3 cells (6.2 MB of fields) 2.97 / 2.90 ms, 64 x 48 x 48
+// (8.3 MB) 3.26 / 3.50, 64^3 (14.7 MB) 3.6 / 4.1.
+constexpr size_t STAGE_COLD = 15 << 19, STAGE_WARM = 16 << 20;
 
 struct Staging {
   unsigned char* p = nullptr;
@@ -53,6 +59,7 @@ struct Pool {
   std::mutex mu;
   std::unique_ptr<Staging> idle[STAGE_KEEP];
   int users = 0;
+  size_t cold = 0;  // bytes of calls that found no idle area, since the first user
   // helper threads, their calls' jobs; helpers of an older `gen` end
   std::vector<std::thread> helpers;
   std::vector<Job*> jobs;
@@ -78,9 +85,10 @@ void pool_in_child() {
   pool_of_process() = p;
 }
 
-// A staging area for stream s, or null where none can be had (s on another
-// device than the current one among them: events belong to a device).
-std::unique_ptr<Staging> take_staging(hipStream_t s) {
+// A staging area for a call of `bytes` on stream s, or null where none is worth
+// making or can be had (s on another device than the current one among them:
+// events belong to a device).
+std::unique_ptr<Staging> take_staging(hipStream_t s, size_t bytes) {
   int dev = 0, sdev = 0;
   if (hipGetDevice(&dev) != hipSuccess || (s && hipStreamGetDevice(s, &sdev) != hipSuccess)) {
     (void)hipGetLastError();
@@ -91,6 +99,8 @@ std::unique_ptr<Staging> take_staging(hipStream_t s) {
     std::lock_guard<std::mutex> lk(pool().mu);
     for (std::unique_ptr<Staging>& st : pool().idle)
       if (st && st->device == dev) return std::move(st);
+    pool().cold += bytes;
+    if (bytes < STAGE_COLD && pool().cold < STAGE_WARM) return nullptr;
   }
   std::unique_ptr<Staging> st(new (std::nothrow) Staging());
   if (!st) return nullptr;
@@ -281,7 +291,7 @@ struct StagingCall {
   std::unique_ptr<Staging> st;
   hipStream_t s;
   bool idle = false;
-  explicit StagingCall(hipStream_t stream) : st(take_staging(stream)), s(stream) {}
+  StagingCall(hipStream_t stream, size_t bytes) : st(take_staging(stream, bytes)), s(stream) {}
   ~StagingCall() {
     if (!st) return;
     if (!idle) (void)hipStreamSynchronize(s);  // (after an error)
@@ -301,6 +311,7 @@ StagingUser::~StagingUser() {
   {
     std::lock_guard<std::mutex> lk(pool().mu);
     if (--pool().users > 0) return;
+    pool().cold = 0;
     std::swap(old, pool().idle);
     ended.swap(pool().helpers);
     ++pool().gen;
@@ -312,7 +323,7 @@ StagingUser::~StagingUser() {
 void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t s,
              const std::function<void(int)>& fill) {
   if (n * bytes >= STAGE_MIN && all_pageable(dst, n) && disjoint(dst, n, bytes)) {
-    StagingCall c(s);
+    StagingCall c(s, n * bytes);
     const Chunks ch(n, bytes);
     unsigned char* const ring = c.st ? c.st->p : nullptr;
     const auto copy = [&](size_t i) {
@@ -354,7 +365,7 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
 void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream_t s,
                const std::function<void(int)>& use) {
   if (n * bytes >= STAGE_MIN && all_pageable(src, n)) {
-    StagingCall c(s);
+    StagingCall c(s, n * bytes);
     const Chunks ch(n, bytes);
     unsigned char* const ring = c.st ? c.st->p : nullptr;
     const auto copy = [&](size_t i) {

@@ -264,6 +264,41 @@ int forked_child() {
   if (!WIFEXITED(st)) return fail("the child did not end by itself");
   return WEXITSTATUS(st) ? fail("the child's fields") : 0;
 }
+
+// A grid that is made, read and freed does not pay for a pinned area that its
+// fields are too small to earn back; one that lives on gets an area, and so
+// does the first transfer of a large one.
+int short_lived() {
+  const size_t count = 48 * 48 * 48;  // 6.2 MB in seven arrays
+  for (int grid = 0; grid < 3; ++grid) {
+    StagingUser user;
+    Seven s(count, true), g(count, false);
+    if (!s.set()) return fail("fields loaded");
+    g.get();
+    if (!g.h.right()) return fail("fields read");
+  }
+  if (fake::pins) return fail("an area was pinned for a short-lived grid");
+  StagingUser user;
+  for (int call = 0; call < 10; ++call) {
+    Seven g(count, false);
+    g.get();
+    if (!g.h.right()) return fail("fields read again");
+  }
+  if (fake::pins != 1) return fail("areas of a grid that lives on");
+  {
+    StagingUser other;
+    Seven g(64 * 64 * 64, false);  // 14.7 MB: with the area that is there
+    g.get();
+  }
+  if (fake::pins != 1) return fail("an idle area was not taken");
+  return 0;
+}
+int large_first() {
+  StagingUser user;
+  Seven s(64 * 64 * 64, true);
+  if (!s.set()) return fail("fields loaded");
+  return fake::pins == 1 ? 0 : fail("areas of a large grid");
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -271,5 +306,7 @@ int main(int argc, char** argv) {
   if (c == "launch_error") return launch_error();
   if (c == "no_memory") return no_memory();
   if (c == "forked_child") return forked_child();
+  if (c == "short_lived") return short_lived();
+  if (c == "large_first") return large_first();
   return fail("unknown case");
 }

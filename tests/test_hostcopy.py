@@ -22,7 +22,8 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["launch_error", "no_memory", "forked_child"])
+@pytest.mark.parametrize("case", ["launch_error", "no_memory", "forked_child", "short_lived",
+                                  "large_first"])
 def test_host_transfers(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, (case, r.returncode, r.stdout[-2000:], r.stderr[-2000:])
