@@ -149,7 +149,9 @@ size_t footprint_bytes(const nfvm_grid_desc& d) {
     b += (size_t)gl.total * (1 + 4 * d.dim + 3 * (l == 0 || wide_level(d, l) ? S0 : SC));
     b += l == 0 ? (size_t)gl.total * 2 : (size_t)gl.total;  // face codes / full flags
   }
-  b += 160 * 1024;                                  // bottom solver's LDS image
+  b += 160 * 1024;                                  // bottom solver's LDS image ...
+  if (d.n_levels >= 3)                              // ... and its top level's constants
+    b += std::min((size_t)level_geom(d, 1).cells(), (size_t)5 * BOTTOM_THREADS) * (10 * 4 + S0);
   b += (size_t)max_blocks_of(g) * RED_MAX_NV * 8 + 4096;  // reduction partials
   b += (size_t)2 * COARSE_MAX * COARSE_MAX * 8 + COARSE_MAX * 4;  // dense coarse inverse
   b += MAX_PATCHES * sizeof(DevPatch) + 5 * 4 * MAX_PATCHES;
