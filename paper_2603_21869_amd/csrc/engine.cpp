@@ -1095,7 +1095,8 @@ class GridT : public GridBase {
 
   // Which levels the bottom solver takes: as many of the lowest ones as have
   // at most one workgroup's LDS of cells (counted as iterates, right-hand side,
-  // face coefficients, damping and class bytes of every cell).
+  // face coefficients, damping and class bytes of every cell), and no more than
+  // the kernel's slots, five cells per thread (160 KiB of LDS hold fewer).
   static size_t al16(size_t v) { return (v + 15) & ~(size_t)15; }
   static size_t faces_bytes(const Geom& g) {
     size_t f = (size_t)(g.nx + 1) * g.ny * g.nz + (size_t)g.nx * (g.ny + 1) * g.nz;
@@ -1171,18 +1172,13 @@ class GridT : public GridBase {
     if (bot.mat_lds) off += mat_bytes;
     bot.const_bytes = (int)(off - bot.const_off);
     bot.lds_bytes = off;
-    if (off > limit) {
-      // (not reached: the layout is smaller than the count above)
-      return;
-    }
+    if (off > limit) return;  // (the layout is smaller than the count above)
     bottom_top = top;
     const int n0 = bot.lv[0].n;
     bot.q = std::max(2, (n0 + BOTTOM_THREADS - 1) / BOTTOM_THREADS);
     bot.cmap = cmap;
-    bot.ncount = ncount;
     bot.ainv = work;
     bot.nco = n_coarse;
-    bot.max_n = COARSE_MAX;
     const size_t t_nb = al16((size_t)4 * n0 * 4), t_cf = al16((size_t)6 * n0 * 4),
                  t_wd = al16(n0 * sizeof(C)), t_img = al16(bot.const_bytes);
     const size_t total = t_nb + t_cf + t_wd + t_img;

@@ -355,15 +355,16 @@ __device__ __forceinline__ double adj_nut(const AdjParams& p, const AdjCell& c) 
 }
 }  // namespace
 
-// The explicit stage's reverse mode: 153 bytes per cell (thirteen dense arrays
+// The explicit stage's reverse mode: 153 bytes per cell (twelve dense arrays
 // in and seven out, with the type byte: it was 603 with the state packed and
 // the weights of every cell stored by one pass and gathered by another).
-// Bound by its FP64 instructions and the two waves per SIMD that its live
-// values leave (about 900 vector instructions per cell and plane): on the
-// 512 x 256 x 128 room 1.52 ms per call, 1.7 TB/s of those bytes, from 3.65 ms
-// for the two passes.  Measured and slower or no faster: predicated loads with
-// zeroed defaults (1.88 ms, spills), 6 rows (2.03), 64-bit lane addresses
-// (1.61), all array pointers kept in scalar registers (1.58).
+// Bound by latency at the two waves per SIMD that its live values leave (235
+// VGPRs; about 900 vector instructions per cell and plane keep the vector
+// units busy 41 % of the time): on the 512 x 256 x 128 room 1.52 ms per call,
+// 1.7 TB/s of those bytes, from 3.65 ms for the two passes.  Measured and slower
+// or no faster: predicated loads with zeroed defaults (1.88 ms, spills), 6 rows
+// (2.03), 64-bit lane addresses (1.61), all array pointers kept in scalar
+// registers (1.58).
 __global__ __launch_bounds__(ABX* EX_RY, 2) void k_adj_explicit(ExplicitArgs a) {
   const AdjParams& p = a.p;
   const uint8_t* __restrict__ type = a.type;

@@ -880,9 +880,12 @@ NFVM_TILE_KERNELS(k_smooth2_code4, smooth2_body, SmoothArgs, (S, C), (class S, c
                   (S, C), MBS, false)
 
 // Whether level l takes two-sweep passes: level 0 with four-cell rows, of
-// more than PAIR_CELLS cells.  A pass saves HBM bytes and pays in halo lanes,
-// barriers and a longer walk; where x, b and the face codes stay in the 256 MB
-// last-level cache between two sweeps it saves nothing.  Measured per
+// more than PAIR_CELLS cells.  A pass reads x, b and the face codes of a tile's
+// halo again (1.48 times its bytes on 134M cells) and pays in halo lanes and
+// barriers, which the second sweep's saved reads repay only where most of them
+// come from memory.  (The 256 MB last-level cache holds x, b and codes of 25M
+// cells in mixed precision, of 14M in FP64, where 16.8M still lose.)  The line
+// is a measured count: both types cross between 16.8M and 33.6M cells.  Per
 // iteration, three sweeps on each side, single / pairs: 2.1M cells (256 x 128 x
 // 64) mixed 208 / 242 us, FP64 273 / 313; 8.4M 492 / 561, 782 / 867; 16.8M
 // 855 / 896, 1396 / 1428; 33.6M 1594 / 1507, 2505 / 2434.
@@ -1736,14 +1739,17 @@ NFVM_TILE_KERNELS(k_chain, chain_body, ChainArgs, (S, C, SC),
                   (S, C, SC, CODE, NSW, RESTR), CH_THREADS, false)
 
 // Whether level l (pre and post sweeps) takes them; cells: of the level's
-// launch, with those of the grids batched with it (level 0: its own).  Past the limits the halo's extra work costs more than the saved
-// launches.  Measured per iteration without / with, FP64, two sweeps on each
-// side: level 0 of 32768 cells 68.9 / 51.1 us, 131072 76.7 / 70.2, 262144
-// 89.8 / 85.3, 393216 104.8 / 108.4; level 1 of 32768 cells 90.2 / 85.5,
-// 131072 134.5 / 133.1, 262144 188.2 / 188.3 (FP32 with three sweeps: slower).
-// Per step of 8 batched grids: level 1 of 8 x 32768 cells 650 / 623 us, level
-// 0 of 8 x 131072 438 / 432, of 8 x 262144 645 / 650.  Levels without
-// smoothing on one side and Algorithm 1's literal form keep the single launches.
+// launch, with those of the grids batched with it (level 0: its own).  The
+// limit is where every form measured still gains; at twice it some do and
+// some lose by the halo's extra work.  Per iteration without / with, FP64, two
+// sweeps on each side: level 0 of 32768 cells 68.9 / 51.1 us, 131072 76.7 /
+// 70.2, 262144 89.8 / 85.3, 393216 104.8 / 108.4; level 1 of 32768 cells 90.2 /
+// 85.5, 131072 134.5 / 133.1, 262144 188.2 / 188.3, and with a limit of 262144
+// cells an FP32 room with three and six sweeps takes 3 to 5 % longer.  Per step
+// of 8 batched grids, whose level 0 is chained as each grid's is alone: level 1
+// of 8 x 32768 cells 650 / 623 us, level 0 of 8 x 131072 438 / 432, of 8 x
+// 262144 645 / 650.  Levels without smoothing on one side and Algorithm 1's
+// literal form keep the single launches.
 constexpr long long CHAIN_CELLS = 1 << 17;
 bool chain_level(const Level& l, int pre, int post, long long cells) {
   return pre >= 1 && post >= 1 && pre <= CHAIN_STEPS && post <= CHAIN_STEPS && l.g.sd == 0.0 &&
@@ -2862,7 +2868,6 @@ __global__ __launch_bounds__(256) void k_bottom_setup(Bottom B) {
     }
   }
   const int n = B.nco;
-  if (n > B.max_n) return;
   const BottomLevel& L = B.lv[B.nlev - 1];
   int* cidx = (int*)(img + B.bcidx);
   for (int a = t; a < n; a += NT) {
@@ -3298,13 +3303,12 @@ __device__ __forceinline__ void bottom_body(const Bottom& B, const SC* __restric
     for (int c = t; c < L.n; c += NT) x[c] = (C)0;  // (inactive cells)
     for (int a = t; a < n; a += NT) bc[a] = b[cidx[a]];
     __syncthreads();
-    if (n <= B.max_n)
-      for (int a = t; a < n; a += NT) {
-        C s = 0;
+    for (int a = t; a < n; a += NT) {
+      C s = 0;
 #pragma unroll 16
-        for (int q = 0; q < n; ++q) s += A[(size_t)q * n + a] * bc[q];
-        x[cidx[a]] = s;
-      }
+      for (int q = 0; q < n; ++q) s += A[(size_t)q * n + a] * bc[q];
+      x[cidx[a]] = s;
+    }
     __syncthreads();
   }
   // ---- up the hierarchy: prolongation and post-smoothing

@@ -386,9 +386,8 @@ struct Bottom {
   double wj;
   BottomLevel lv[BOTTOM_MAX_LEVELS];
   const int* cmap;  // padded indices of the coarsest active cells
-  const int* ncount;
   const double* ainv;
-  int nco, max_n;
+  int nco;  // how many there are
   // the coarsest level's inverse, transposed, in the compute type; in LDS (at
   // bmat) or, when it does not fit or has more than 64 rows, read from memory
   void* mat;
