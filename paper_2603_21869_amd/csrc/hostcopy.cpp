@@ -1,9 +1,12 @@
 // Transfers of a grid's fields.  The runtime's copy of pageable memory stages
 // through its own pinned buffers with one host thread, which also takes the
-// page faults of a result array's first touch: 9 GB/s into fresh arrays and
-// 27 GB/s out of touched ones (470 MB in seven arrays), against 24 and 38 here,
-// where the device's copy engine moves chunks between the device and a pinned
-// ring and up to COPY_THREADS threads between the ring and the arrays.
+// page faults of a result array's first touch: 10 GB/s into fresh arrays and
+// 27 GB/s out of touched ones (940 MB in seven arrays), against 32 and 48 here,
+// where a kernel moves chunks between the device and a pinned ring and up to
+// COPY_THREADS threads between the ring and the arrays.  (Not the copy engine:
+// the driver clears freed device memory with it, 34 ms per GB, and chunks then
+// wait for it.  Fields of 7.5 GB into a grid made after a 22 GB one was freed:
+// 377 ms through the engine, 228 with the runtime's copy, 155 here.)
 #include "hostcopy.hpp"
 
 #include <pthread.h>
@@ -24,16 +27,18 @@
 namespace nfvm {
 namespace {
 
-// 470 MB into the device / into fresh arrays: chunks of 1 MiB 15.4 / 21.4 ms (a
-// device copy has a fixed cost), 2 MiB 12.3 / 19.6, 4 MiB no better at twice
-// the pinned memory; one thread 18.0 / 42.6, two 12.2 / 24.7.  More than four
-// threads share the same memory channels (no gain).
+// 940 MB into the device / into fresh arrays: chunks of 1 MiB 22.3 / 35.2 ms (a
+// launch and its event have a fixed cost), 2 MiB 19.7 / 29.7, 4 MiB 18.6 / 26.7
+// at twice the pinned memory; four slots 26.9 / 46.3; one thread 33.9 / 68.7,
+// two 19.7 / 39.6, six 19.7 / 31.4.
 constexpr size_t CHUNK = 2 << 20;
 constexpr int SLOTS = 8;         // chunks of a staging area
 constexpr int COPY_THREADS = 4;  // the calling one and its helpers
 constexpr int STAGE_KEEP = 2;    // idle areas kept, 16 MiB each
-// Below this many bytes a call stays with the runtime's copy (seven arrays of
-// 0.13 MB: 0.29 ms with the ring, 0.24 without; of 8.4 MB: 3.3 against 9.2).
+// Below this many bytes a call stays with the runtime's copy: it moves them
+// about as fast, and a grid need not make a ring and threads for them.  Out of
+// the device into fresh arrays, with the ring / without: 3.7 MB 0.2 / 0.3 ms,
+// 8.3 MB 1.0 / 2.0, 14.7 MB 1.7 / 3.5.
 constexpr size_t STAGE_MIN = 4 << 20;
 // An area and the helper threads cost 0.2 ms to make and end, for every grid of
 // a program that has one grid at a time (they end with the last).  Without an
@@ -45,6 +50,7 @@ constexpr size_t STAGE_COLD = 15 << 19, STAGE_WARM = 16 << 20;
 
 struct Staging {
   unsigned char* p = nullptr;
+  unsigned char* d = nullptr;  // as the device addresses it
   hipEvent_t ev[SLOTS] = {};
   int device = 0;
   ~Staging() {
@@ -105,7 +111,9 @@ std::unique_ptr<Staging> take_staging(hipStream_t s, size_t bytes) {
   std::unique_ptr<Staging> st(new (std::nothrow) Staging());
   if (!st) return nullptr;
   st->device = dev;
-  bool ok = hipHostMalloc((void**)&st->p, CHUNK * SLOTS, hipHostMallocDefault) == hipSuccess;
+  bool ok = hipHostMalloc((void**)&st->p, CHUNK * SLOTS,
+                          hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
+            hipHostGetDevicePointer((void**)&st->d, st->p, 0) == hipSuccess;
   for (int i = 0; ok && i < SLOTS; ++i)
     ok = hipEventCreateWithFlags(&st->ev[i], hipEventDisableTiming) == hipSuccess;
   if (!ok) {
@@ -266,13 +274,19 @@ std::unique_ptr<Job> make_job(size_t chunks, const ChunkCopy& copy) {
   }
 }
 
-// fn(f), which launches kernels: a launch that fails leaves its code as the
+// fn(), which launches kernels: a launch that fails leaves its code as the
 // thread's last error, which is taken here, before an event query that is not
 // ready overwrites it.  (An error from before the call is not the call's.)
-void launched(const std::function<void(int)>& fn, int f) {
+template <class F>
+void launched(F&& fn) {
   const bool clean = hipPeekAtLastError() == hipSuccess;
-  fn(f);
+  fn();
   if (clean) NFVM_CK(hipGetLastError());
+}
+
+// Whether a call's device buffer can be copied by launch_copy_values.
+bool copyable(const void* dev, size_t bytes) {
+  return (uintptr_t)dev % 16 == 0 && bytes % sizeof(double) == 0;
 }
 
 // Whether the device has passed an event.
@@ -322,7 +336,8 @@ StagingUser::~StagingUser() {
 
 void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t s,
              const std::function<void(int)>& fill) {
-  if (n * bytes >= STAGE_MIN && all_pageable(dst, n) && disjoint(dst, n, bytes)) {
+  if (n * bytes >= STAGE_MIN && copyable(dev, bytes) && all_pageable(dst, n) &&
+      disjoint(dst, n, bytes)) {
     StagingCall c(s, n * bytes);
     const Chunks ch(n, bytes);
     unsigned char* const ring = c.st ? c.st->p : nullptr;
@@ -333,10 +348,12 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
       size_t issued = 0, arrived = 0, copied = 0;  // device copies begun, ended; chunks done
       while (copied < ch.total) {
         for (; issued < ch.total && issued < copied + SLOTS; ++issued) {
-          if (ch.off(issued) == 0) launched(fill, ch.array(issued));
-          NFVM_CK(hipMemcpyAsync(ring + issued % SLOTS * CHUNK,
-                                 (const unsigned char*)dev + ch.off(issued), ch.len(issued),
-                                 hipMemcpyDeviceToHost, s));
+          launched([&] {
+            if (ch.off(issued) == 0) fill(ch.array(issued));
+            launch_copy_values((const double*)((const unsigned char*)dev + ch.off(issued)),
+                               (double*)(c.st->d + issued % SLOTS * CHUNK),
+                               (int)(ch.len(issued) / sizeof(double)), s);
+          });
           NFVM_CK(hipEventRecord(c.st->ev[issued % SLOTS], s));
         }
         size_t now = arrived;
@@ -356,7 +373,7 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
     }
   }
   for (int f = 0; f < n; ++f) {
-    launched(fill, f);
+    launched([&] { fill(f); });
     NFVM_CK(hipMemcpyAsync(dst[f], dev, bytes, hipMemcpyDeviceToHost, s));
     NFVM_CK(hipStreamSynchronize(s));
   }
@@ -364,7 +381,7 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
 
 void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream_t s,
                const std::function<void(int)>& use) {
-  if (n * bytes >= STAGE_MIN && all_pageable(src, n)) {
+  if (n * bytes >= STAGE_MIN && copyable(dev, bytes) && all_pageable(src, n)) {
     StagingCall c(s, n * bytes);
     const Chunks ch(n, bytes);
     unsigned char* const ring = c.st ? c.st->p : nullptr;
@@ -377,11 +394,14 @@ void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream
       job->ready(SLOTS);
       while (issued < ch.total) {
         for (; issued < copied; ++issued) {
-          NFVM_CK(hipMemcpyAsync((unsigned char*)dev + ch.off(issued),
-                                 ring + issued % SLOTS * CHUNK, ch.len(issued),
-                                 hipMemcpyHostToDevice, s));
+          launched([&] {
+            launch_copy_values((const double*)(c.st->d + issued % SLOTS * CHUNK),
+                               (double*)((unsigned char*)dev + ch.off(issued)),
+                               (int)(ch.len(issued) / sizeof(double)), s);
+          });
           NFVM_CK(hipEventRecord(c.st->ev[issued % SLOTS], s));
-          if (ch.off(issued) + ch.len(issued) == bytes) launched(use, ch.array(issued));
+          if (ch.off(issued) + ch.len(issued) == bytes)
+            launched([&] { use(ch.array(issued)); });
         }
         size_t now = freed;
         while (now < issued && ended(c.st->ev[now % SLOTS])) ++now;
@@ -403,7 +423,7 @@ void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream
   }
   for (int f = 0; f < n; ++f) {
     NFVM_CK(hipMemcpyAsync(dev, src[f], bytes, hipMemcpyHostToDevice, s));
-    launched(use, f);
+    launched([&] { use(f); });
     NFVM_CK(hipStreamSynchronize(s));
   }
 }

@@ -272,6 +272,8 @@ template <class F>
 void launch_pack(const Geom& g, const double* dense, F* padded, double offset, hipStream_t s);
 template <class F>
 void launch_unpack(const Geom& g, const F* padded, double* dense, double offset, hipStream_t s);
+// dst = src, n values, both 16-byte aligned, one of them pinned host memory.
+void launch_copy_values(const double* src, double* dst, int n, hipStream_t s);
 
 // Velocity in V, transported scalars (T, k, omega) in F.
 template <class V, class F>

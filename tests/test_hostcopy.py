@@ -23,7 +23,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case", ["launch_error", "no_memory", "forked_child", "short_lived",
-                                  "large_first"])
+                                  "large_first", "no_copy_engine"])
 def test_host_transfers(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, (case, r.returncode, r.stdout[-2000:], r.stderr[-2000:])
