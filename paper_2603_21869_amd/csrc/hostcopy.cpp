@@ -43,9 +43,10 @@ constexpr size_t STAGE_MIN = 4 << 20;
 // An area and the helper threads cost 0.2 ms to make and end, for every grid of
 // a program that has one grid at a time (they end with the last).  Without an
 // idle area, a call of fewer than STAGE_COLD bytes makes one only once such
-// calls have moved STAGE_WARM bytes.  Made, read and freed, a mixed-precision
-// grid with the ring / without: 48^3 cells (6.2 MB of fields) 2.97 / 2.90 ms, 64 x 48 x 48
-// (8.3 MB) 3.26 / 3.50, 64^3 (14.7 MB) 3.6 / 4.1.
+// calls have moved STAGE_WARM bytes.  Made and freed / made, read and freed, a
+// mixed-precision grid of 48^3 cells (6.2 MB of fields) 2.55 / 2.83 ms with the
+// ring, 2.50 / 2.94 without; 64 x 48 x 48 (8.3 MB) 2.77 / 3.08, 2.85 / 3.48;
+// 64^3 (14.7 MB) 2.97 / 3.62, 3.09 / 4.17.
 constexpr size_t STAGE_COLD = 15 << 19, STAGE_WARM = 16 << 20;
 
 struct Staging {
