@@ -2,6 +2,7 @@
 // order of kernels in a time step (Sec. 2.6: destruction over dt/2, explicit
 // step, projection, destruction over dt/2) and in the pressure solve.
 #include "engine.hpp"
+#include "fastest.hpp"
 #include "post.hpp"
 
 #include <math.h>
@@ -586,16 +587,13 @@ class GridT : public GridBase {
     // served grids never tune: the choice of the tuned shape nearest in
     // size, else the default
     if (tune_cached_only) return tune_lookup_near(key, &cached) ? cached : TILE_DEFAULT;
-    int best = TILE_DEFAULT;
-    float bt = 1e30f;
-    for (int ci = 0; ci < N_TILE_CANDIDATES; ++ci) {
-      const int c = cand[ci];
-      const float t = time_it([&] { launch(c); });
-      if (t < bt) {
-        bt = t;
-        best = c;
-      }
-    }
+    // (these targets set the order of sums, and with it a solve's last bits; the
+    // update's, which does too, is not measured again: its first candidate is
+    // slow only the first time, and its choices are steady)
+    const bool settle = kid == TK_START || kid == TK_APPLY;
+    const int best = cand[fastest(N_TILE_CANDIDATES, settle, [&](int ci) {
+      return time_it([&] { launch(cand[ci]); });
+    })];
     tune_store(key, best);
     return best;
   }
