@@ -360,7 +360,7 @@ __device__ __forceinline__ double adj_nut(const AdjParams& p, const AdjCell& c) 
 // the weights of every cell stored by one pass and gathered by another).
 // Bound by latency at the two waves per SIMD that its live values leave (235
 // VGPRs; about 900 vector instructions per cell and plane keep the vector
-// units busy 41 % of the time): on the 512 x 256 x 128 room 1.52 ms per call,
+// units busy 45 % of the time): on the 512 x 256 x 128 room 1.52 ms per call,
 // 1.7 TB/s of those bytes, from 3.65 ms for the two passes.  Measured and slower
 // or no faster: predicated loads with zeroed defaults (1.88 ms, spills), 6 rows
 // (2.03), 64-bit lane addresses (1.61), all array pointers kept in scalar
@@ -843,10 +843,10 @@ struct DesCell {
 }  // namespace
 
 // The destruction step's reverse mode: 97 bytes per cell (it was 474 with the
-// fifteen weights of every cell stored and gathered).  Bound by FP64 issue and
-// latency at three waves per SIMD: 0.78 ms per call on the 512 x 256 x 128
-// room, from 2.71 ms for the two passes.  Four waves per SIMD (128 VGPRs)
-// spill 130 registers: 2.16 ms.
+// fifteen weights of every cell stored and gathered).  Bound by latency at
+// three waves per SIMD (vector units busy 44 % of the time): 0.78 ms per call on
+// the 512 x 256 x 128 room, from 2.71 ms for the two passes.  Four waves per
+// SIMD (128 VGPRs) spill 130 registers: 2.16 ms.
 __global__ __launch_bounds__(ABX* DS_RY, 3) void k_adj_destroy(AdjParams p,
                                                             const uint8_t* __restrict__ type,
                                                             const DevPatch* __restrict__ pt,
