@@ -714,7 +714,7 @@ class GridT : public GridBase {
     const double* src[7] = {in->u, in->v, in->w, in->T, in->k, in->omega, in->p};
     for (int f = 0; f < 7; ++f)
       if (!src[f]) throw Error{NFVM_E_INVAL, "all seven field pointers are required"};
-    to_device(stage, (const void* const*)src, 7, (size_t)ncells * sizeof(double), stream,
+    to_device(stage, (const void* const*)src, 7, (size_t)ncells * sizeof(double), stream, served,
               [&](int f) {
                 if (f < 3)
                   launch_pack<V>(g, stage, vcur(f), 0.0, stream);
@@ -733,20 +733,21 @@ class GridT : public GridBase {
     double* dst[7] = {out->u, out->v, out->w, out->T, out->k, out->omega, out->p};
     for (int f = 0; f < 7; ++f)
       if (!dst[f]) throw Error{NFVM_E_INVAL, "all seven field pointers are required"};
-    to_host(stage, (void* const*)dst, 7, (size_t)ncells * sizeof(double), stream, [&](int f) {
-      if (f < 3)
-        launch_unpack<V>(g, vcur(f), stage, 0.0, stream);
-      else if (f < 6)
-        launch_unpack<F>(g, scur(f), stage, f == 3 ? ph.T_ref : 0.0, stream);
-      else
-        launch_unpack<P>(g, p, stage, 0.0, stream);
-    });
+    to_host(stage, (void* const*)dst, 7, (size_t)ncells * sizeof(double), stream, served,
+            [&](int f) {
+              if (f < 3)
+                launch_unpack<V>(g, vcur(f), stage, 0.0, stream);
+              else if (f < 6)
+                launch_unpack<F>(g, scur(f), stage, f == 3 ? ph.T_ref : 0.0, stream);
+              else
+                launch_unpack<P>(g, p, stage, 0.0, stream);
+            });
   }
 
   void lambda2(double* out) override {
     if (!out) throw Error{NFVM_E_INVAL, "an output array is required"};
     void* dst[1] = {out};
-    to_host(stage, dst, 1, (size_t)ncells * sizeof(double), stream, [&](int) {
+    to_host(stage, dst, 1, (size_t)ncells * sizeof(double), stream, served, [&](int) {
       launch_lambda2<V>(g, ph, type, patches, vcur(0), vcur(1), vcur(2), stage, stream);
       NFVM_CK(hipGetLastError());
     });
@@ -1995,6 +1996,7 @@ std::unique_ptr<GridBase> make_grid(const nfvm_grid_desc& d, const nfvm_fields* 
   else
     gb.reset(new GridMixed());
   gb->use_autotune = tune_mode != 0;
+  gb->served = tune_mode == 2;
   if (tune_mode == 2) {
     if (d.precision == NFVM_FP64)
       static_cast<GridFP64*>(gb.get())->tune_cached_only = true;

@@ -95,6 +95,7 @@ class GridBase {
   StagingUser staging;
 
  public:
+  bool served = false;  // one of a server's grids: others' kernels run beside its transfers
   virtual ~GridBase() = default;
   virtual void step(int n, nfvm_step_stats* st, nfvm_status* status) = 0;
 

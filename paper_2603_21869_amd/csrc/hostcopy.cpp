@@ -6,7 +6,10 @@
 // COPY_THREADS threads between the ring and the arrays.  (Not the copy engine:
 // the driver clears freed device memory with it, 34 ms per GB, and chunks then
 // wait for it.  Fields of 7.5 GB into a grid made after a 22 GB one was freed:
-// 377 ms through the engine, 228 with the runtime's copy, 155 here.)
+// 377 ms through the engine, 228 with the runtime's copy, 155 here.  Beside
+// other lanes' kernels, in a server, the copy kernel waits for compute units
+// and the engine is the better one all the same: 256 requests on 9 slots 2116
+// Mcell-steps/s with it, 2050 with the kernel, 1845 with the runtime's copy.)
 #include "hostcopy.hpp"
 
 #include <pthread.h>
@@ -285,7 +288,10 @@ void launched(F&& fn) {
   if (clean) NFVM_CK(hipGetLastError());
 }
 
-// Whether a call's device buffer can be copied by launch_copy_values.
+void copy_values(const void* src, void* dst, size_t bytes, hipStream_t s) {
+  launch_copy_values((const double*)src, (double*)dst, (int)(bytes / sizeof(double)), s);
+}
+// Whether a call's device buffer can be copied by it.
 bool copyable(const void* dev, size_t bytes) {
   return (uintptr_t)dev % 16 == 0 && bytes % sizeof(double) == 0;
 }
@@ -335,7 +341,7 @@ StagingUser::~StagingUser() {
   for (std::thread& t : ended) t.join();
 }
 
-void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t s,
+void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t s, bool engine,
              const std::function<void(int)>& fill) {
   if (n * bytes >= STAGE_MIN && copyable(dev, bytes) && all_pageable(dst, n) &&
       disjoint(dst, n, bytes)) {
@@ -349,12 +355,13 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
       size_t issued = 0, arrived = 0, copied = 0;  // device copies begun, ended; chunks done
       while (copied < ch.total) {
         for (; issued < ch.total && issued < copied + SLOTS; ++issued) {
-          launched([&] {
-            if (ch.off(issued) == 0) fill(ch.array(issued));
-            launch_copy_values((const double*)((const unsigned char*)dev + ch.off(issued)),
-                               (double*)(c.st->d + issued % SLOTS * CHUNK),
-                               (int)(ch.len(issued) / sizeof(double)), s);
-          });
+          if (ch.off(issued) == 0) launched([&] { fill(ch.array(issued)); });
+          const unsigned char* from = (const unsigned char*)dev + ch.off(issued);
+          const size_t slot = issued % SLOTS * CHUNK, len = ch.len(issued);
+          if (engine)
+            NFVM_CK(hipMemcpyAsync(ring + slot, from, len, hipMemcpyDeviceToHost, s));
+          else
+            launched([&] { copy_values(from, c.st->d + slot, len, s); });
           NFVM_CK(hipEventRecord(c.st->ev[issued % SLOTS], s));
         }
         size_t now = arrived;
@@ -380,7 +387,7 @@ void to_host(const void* dev, void* const* dst, int n, size_t bytes, hipStream_t
   }
 }
 
-void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream_t s,
+void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream_t s, bool engine,
                const std::function<void(int)>& use) {
   if (n * bytes >= STAGE_MIN && copyable(dev, bytes) && all_pageable(src, n)) {
     StagingCall c(s, n * bytes);
@@ -395,11 +402,12 @@ void to_device(void* dev, const void* const* src, int n, size_t bytes, hipStream
       job->ready(SLOTS);
       while (issued < ch.total) {
         for (; issued < copied; ++issued) {
-          launched([&] {
-            launch_copy_values((const double*)(c.st->d + issued % SLOTS * CHUNK),
-                               (double*)((unsigned char*)dev + ch.off(issued)),
-                               (int)(ch.len(issued) / sizeof(double)), s);
-          });
+          unsigned char* to = (unsigned char*)dev + ch.off(issued);
+          const size_t slot = issued % SLOTS * CHUNK, len = ch.len(issued);
+          if (engine)
+            NFVM_CK(hipMemcpyAsync(to, ring + slot, len, hipMemcpyHostToDevice, s));
+          else
+            launched([&] { copy_values(c.st->d + slot, to, len, s); });
           NFVM_CK(hipEventRecord(c.st->ev[issued % SLOTS], s));
           if (ch.off(issued) + ch.len(issued) == bytes)
             launched([&] { use(ch.array(issued)); });

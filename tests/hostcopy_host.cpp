@@ -134,8 +134,8 @@ struct Seven {
   Seven(size_t count, bool fill) : h(7, count, fill), dev(count), p(h.ptrs()) {}
   size_t bytes() const { return h.count * sizeof(double); }
   // (get: the kernel that writes dev; set: the one that reads it)
-  void get(int bad = -1) {
-    to_host(dev.data(), p.data(), 7, bytes(), nullptr, [&](int f) {
+  void get(int bad = -1, bool engine = false) {
+    to_host(dev.data(), p.data(), 7, bytes(), nullptr, engine, [&](int f) {
       if (f == bad) {
         fake::set(hipErrorInvalidConfiguration);  // a launch that fails leaves its code
         return;
@@ -143,9 +143,9 @@ struct Seven {
       for (size_t i = 0; i < h.count; ++i) dev[i] = Arrays::value(f, i);
     });
   }
-  bool set(int bad = -1) {
+  bool set(int bad = -1, bool engine = false) {
     bool ok = true;
-    to_device(dev.data(), p.data(), 7, bytes(), nullptr, [&](int f) {
+    to_device(dev.data(), p.data(), 7, bytes(), nullptr, engine, [&](int f) {
       if (f == bad) {
         fake::set(hipErrorInvalidConfiguration);
         return;
@@ -177,6 +177,8 @@ int launch_error() {
       Seven g(count, false), s(count, true);
       if (!throws([&] { g.get(bad); })) return fail("a field that was not unpacked was returned");
       if (!throws([&] { s.set(bad); })) return fail("a field that was not packed was accepted");
+      if (!throws([&] { g.get(bad, true); }) || !throws([&] { s.set(bad, true); }))
+        return fail("a failed launch beside the copy engine");
     }
     Seven g(count, false);
     fake::last = hipErrorInvalidValue;
@@ -222,7 +224,7 @@ int no_memory() {
     const std::function<void(int)> fill = [&g](int f) {
       for (size_t i = 0; i < g.h.count; ++i) g.dev[i] = Arrays::value(f, i);
     };
-    return denying(n, [&] { to_host(g.dev.data(), g.p.data(), 7, bytes, nullptr, fill); }) &&
+    return denying(n, [&] { to_host(g.dev.data(), g.p.data(), 7, bytes, nullptr, false, fill); }) &&
            g.h.right();
   });
   if (rc) return rc;
@@ -236,7 +238,7 @@ int no_memory() {
     const std::function<void(int)> use = [&c](int f) {
       for (size_t i = 0; i < c.s.h.count; ++i) c.ok = c.ok && c.s.dev[i] == Arrays::value(f, i);
     };
-    return denying(n, [&] { to_device(s.dev.data(), s.p.data(), 7, bytes, nullptr, use); }) && ok;
+    return denying(n, [&] { to_device(s.dev.data(), s.p.data(), 7, bytes, nullptr, false, use); }) && ok;
   });
   if (rc) return rc;
   return each_allocation([&](int n) {
@@ -300,15 +302,18 @@ int short_lived() {
   if (fake::pins != 1) return fail("an idle area was not taken");
   return 0;
 }
-// Large transfers do not pass through the copy engine, which the driver keeps
-// busy after a large allocation is freed.
+// Large transfers pass through the copy engine, which the driver keeps busy
+// after a large allocation is freed, only where that is asked for.
 int no_copy_engine() {
   StagingUser user;
-  Seven s(300001, true), g(300001, false);
-  if (!s.set()) return fail("fields loaded");
-  g.get();
-  if (!g.h.right()) return fail("fields read");
-  return fake::copies ? fail("the runtime's copy was called") : 0;
+  for (bool engine : {false, true}) {
+    Seven s(300001, true), g(300001, false);
+    if (!s.set(-1, engine)) return fail("fields loaded");
+    g.get(-1, engine);
+    if (!g.h.right()) return fail("fields read");
+    if (engine != (fake::copies > 0)) return fail("the way of the chunks");
+  }
+  return 0;
 }
 int large_first() {
   StagingUser user;
